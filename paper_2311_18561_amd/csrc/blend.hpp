@@ -156,10 +156,23 @@ __device__ __forceinline__ float pair_exp2(float qz, float c1, float c0, float d
   return fmaf(fmaf(qz, dy, c1), dy, c0);
 }
 
+// A pair whose alpha needs neither the 0.99 clamp nor the test for a positive
+// exponent, for any pixel: o <= 0.99, and a conic far enough from singular
+// that the computed p2 cannot round above 0.  With r = |B| / sqrt(A C),
+// -p2 >= (1 - r) (|q.x| dx^2 + |q.z| dy^2) while the roundings of p2 add at
+// most (2 + 2 r) 2^-24 of the same sum, so r <= 1 - 5e-6 leaves a factor of
+// twenty.  NaNs and infinities fail the test.
+__device__ __forceinline__ bool pair_is_plain(float2 m, float4 co) {
+  return co.w <= kAlphaMax && co.x > 0.0f && co.z > 0.0f && co.y * co.y <= (co.x * co.z) * 0.99999f &&
+         fabsf(m.x) < 1e9f && fabsf(m.y) < 1e9f;
+}
+
+constexpr float kNever = __builtin_huge_valf();  // threshold of a pixel that takes no further pair
+
 constexpr int kPix = 4;  // pixels per lane
 
-// The forward walks a batch's pairs in groups of kGroup (a batch is padded
-// with pairs no pixel uses up to a whole group).
+// The feature forward walks a batch's pairs in groups of kGroup (a batch is
+// padded with pairs no pixel uses up to a whole group).
 constexpr int kGroup = 4;
 __device__ __forceinline__ int pad_to(int cnt) { return (cnt + kGroup - 1) / kGroup * kGroup; }
 

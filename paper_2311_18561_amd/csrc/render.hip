@@ -1,7 +1,8 @@
 // Per-tile alpha blending (Sec. 3.1, Eq. (3)) and its adjoint on gfx950.
 //
-// One 64-lane wavefront owns one 16x16 tile; lane l shades the four pixels of
-// column l % 16 in rows l / 16 + {0, 4, 8, 12}.  The tile's depth-ordered list
+// One 64-lane wavefront owns one 16x16 tile (in the forward, a half or a
+// quarter of one where the image has few tiles); lane l shades the four
+// pixels of column l % 16 in rows l / 16 + {0, 4, 8, 12}.  The tile's depth-ordered list
 // is walked in batches of 64 Gaussians: each lane gathers one Gaussian's
 // record (2D mean, conic, opacity, colour) into LDS and every lane then reads
 // the batch back as broadcasts.  A pixel stops before the Gaussian that would
@@ -21,52 +22,91 @@
 // Tiles reach the eight XCDs in row-sized chunks dealt round-robin
 // (xcd_tile), which balances the XCDs' work and keeps a chunk's shared
 // Gaussians in one L2.
+#include <type_traits>
+
 #include "blend.hpp"
 
 namespace pvg {
 
+// Waves per tile of the forward walk, by the launch's tiles (batched: its
+// bound).  The chip has 1,024 SIMDs and a wave alone issues at about a third
+// of a SIMD's rate, so a launch needs several waves a SIMD; a split tile
+// walks its list once per strip, which costs the per-pair work again.
+// Whole tiles / halves / quarters, us: 48 tiles 19.8 / 12.6 / 9.6, 117 tiles
+// 25.6 / 16.0 / 12.0, 2,400 tiles 66.6 / 55.1 / 59.6, 9,600 tiles 136.5 /
+// 140.2 / 165.6.
+static int forward_parts(int64_t tiles) { return tiles <= 1024 ? 4 : tiles <= 4096 ? 2 : 1; }
+
+// Pairs per group of the walk: enough independent work for a lane with one
+// pixel, few enough live weights for one with four.
+constexpr int forward_group(int px) { return px == 1 ? 8 : 4; }
 
 // kCh: also blend each Gaussian's camera depth, mean velocity and
 // staticness into the channels the view asks for (the flexible rendering of
 // Sec. 3.1, with these in place of the colour).
-template <bool kCount, bool kCulled, bool kCh>
+// kPx: pixels per lane.  A wave takes kPx / 4 of a tile, a strip of 4 kPx of
+// its rows (forward_parts has the rule): block b is strip b mod (4 / kPx) of
+// its tile, and each wave walks the tile's list by itself.
+// kTest: drop listed Gaussians that cannot reach the strip (rectangle lists,
+// and the strips of split tiles); otherwise every listed one is walked.
+template <bool kCount, bool kTest, bool kCh, int kPx>
 __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const uint32_t* __restrict__ vals,
                                                    const uint32_t* __restrict__ ranges,
                                                    unsigned long long* pair_counter) {
+  constexpr int kParts = 4 / kPx;
+  constexpr int kGroup = forward_group(kPx);
   __shared__ float2 s_xy[64];
   __shared__ float4 s_co[64];
   __shared__ float4 s_rgb[64];  // rgb and the list position (as int bits)
   __shared__ float s_z[kCh ? 64 : 1];
   __shared__ float4 s_fv[kCh ? 64 : 1];  // v~ and rho
   const int64_t ntiles = live_tiles(vs);
-  const int64_t tile = xcd_tile(blockIdx.x, vs.total_tiles);
+  const int64_t tile = xcd_tile(static_cast<int64_t>(blockIdx.x) / (8 * kParts) * 8 + (blockIdx.x & 7), vs.total_tiles);
+  const int part = static_cast<int>(blockIdx.x >> 3) % kParts;
   if (tile >= ntiles) return;
   const View& v = view_at(vs, view_of_tile(vs, tile));
   const int64_t local = tile - v.tile_off;
   const int tx = static_cast<int>(local % v.GX), ty = static_cast<int>(local / v.GX);
+  const int row0 = ty * kTile + 4 * kPx * part;  // the strip's first row
+  if (row0 >= v.H) return;
   const int lane = threadIdx.x;
   const int px = tx * kTile + (lane & 15);
-  const int py0 = ty * kTile + (lane >> 4);
+  const int py0 = row0 + (lane >> 4);
   const float fpx = static_cast<float>(px);
-  float X0, X1, Y0, Y1;
-  tile_bounds(tx, ty, v.W, v.H, X0, X1, Y0, Y1);
+  const float X0 = static_cast<float>(tx * kTile), X1 = static_cast<float>(min(v.W, (tx + 1) * kTile) - 1);
+  const float Y0 = static_cast<float>(row0), Y1 = static_cast<float>(min(v.H, row0 + 4 * kPx) - 1);
   const uint64_t lt = (1ull << lane) - 1ull;
-  float T[kPix], Cr[kPix], Cg[kPix], Cb[kPix], Dz[kPix], V0[kPix], V1[kPix], V2[kPix], Rh[kPix];
-  float Aw[kPix];  // sum T alpha, the normalized depth's denominator
-  int last[kPix];
-  bool act[kPix];
+  float T[kPx], Cr[kPx], Cg[kPx], Cb[kPx], Dz[kPx], V0[kPx], V1[kPx], V2[kPx], Rh[kPx];
+  float Aw[kPx];  // sum T alpha, the normalized depth's denominator
+  int last[kPx];
+  float thr[kPx];       // alpha a pair needs to be used: 1/255, or infinity once the pixel has stopped
+  uint64_t live = 0;    // lanes with a pixel that has not stopped
 #pragma unroll
-  for (int k = 0; k < kPix; ++k) {
+  for (int k = 0; k < kPx; ++k) {
     T[k] = 1.0f; Cr[k] = 0.0f; Cg[k] = 0.0f; Cb[k] = 0.0f; last[k] = 0;
     Dz[k] = 0.0f; V0[k] = 0.0f; V1[k] = 0.0f; V2[k] = 0.0f; Rh[k] = 0.0f; Aw[k] = 0.0f;
-    act[k] = px < v.W && py0 + 4 * k < v.H;
+    const bool in = px < v.W && py0 + 4 * k < v.H;
+    thr[k] = in ? kAlphaMin : kNever;
+    live |= __ballot(in);
   }
+  auto blend = [&](int k, const float4& cc, float gz, const float4& gv, float w) {
+    Cr[k] = fmaf(cc.x, w, Cr[k]);
+    Cg[k] = fmaf(cc.y, w, Cg[k]);
+    Cb[k] = fmaf(cc.z, w, Cb[k]);
+    if (kCh) {
+      Dz[k] = fmaf(gz, w, Dz[k]);
+      Aw[k] += w;
+      V0[k] = fmaf(gv.x, w, V0[k]);
+      V1[k] = fmaf(gv.y, w, V1[k]);
+      V2[k] = fmaf(gv.z, w, V2[k]);
+      Rh[k] = fmaf(gv.w, w, Rh[k]);
+    }
+  };
   const uint32_t start = ranges[2 * tile], end = ranges[2 * tile + 1];
   long long evaluated = 0;
-  for (uint32_t b0 = start; b0 < end; b0 += 64) {
-    if (!__any(act[0] || act[1] || act[2] || act[3])) break;
+  for (uint32_t b0 = start; b0 < end && live; b0 += 64) {
     const uint32_t idx = b0 + lane;
-    bool keep = false;
+    bool keep = false, plain = true;
     float2 m;
     float4 co, c;
     float z = 0.0f;
@@ -81,7 +121,8 @@ __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const 
         z = geom.depth[g];
         if (geom.feat) fv = reinterpret_cast<const float4*>(geom.feat)[g];
       }
-      keep = kCulled || tile_reachable(m.x, m.y, co.x, co.y, co.z, co.w, X0, X1, Y0, Y1);
+      keep = !kTest || tile_reachable(m.x, m.y, co.x, co.y, co.z, co.w, X0, X1, Y0, Y1);
+      plain = !keep || pair_is_plain(m, co);
     }
     const uint64_t km = __ballot(keep);
     const int cnt = __popcll(km);
@@ -95,7 +136,7 @@ __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const 
         s_fv[slot] = fv;
       }
     }
-    if (lane >= cnt && lane < pad_to(cnt)) {
+    if (lane >= cnt && lane < (cnt + kGroup - 1) / kGroup * kGroup) {
       // padding up to a whole group (the lane may also have filled a slot
       // below cnt): opacity 0 gives alpha = 0, which no pixel uses, and
       // finite values keep the blends' products at 0
@@ -108,55 +149,105 @@ __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const 
       }
     }
     __syncthreads();
-    // Pairs go in groups of kGroup with one test for a finished wave per
-    // group, so the pixels' active flags stay in scalar lane masks through a
-    // group instead of being carried in vector registers from pair to pair.
-    for (int j0 = 0; j0 < cnt; j0 += kGroup) {
-      if (!__any(act[0] || act[1] || act[2] || act[3])) break;
+    // Pairs go in groups of kGroup.  The walk is bound by VALU issue, so the
+    // common path holds only what every pixel needs: a stopped pixel is one
+    // whose threshold no alpha passes, an unused pair takes alpha = 0 (which
+    // leaves T and the sums as they are), and whether a pixel stops is asked
+    // once per group (T only falls, so its value behind the group tells).  A
+    // tile's pixels stop within a few pairs of each other (0.5 pairs before
+    // the tile's end on average on the 1M-Gaussian driving path, 5 on the
+    // 200k box), so only a walk's last groups take the second path, pair by
+    // pair with the stop test.
+    auto walk = [&](auto plain_pairs) {
+      constexpr bool kPlain = decltype(plain_pairs)::value;
+      for (int j0 = 0;; j0 += kGroup) {
+        bool stopped = false;
+        for (; j0 < cnt; j0 += kGroup) {
+          float w[kGroup][kPx], Tn[kPx];
+          bool ok[kGroup][kPx];
 #pragma unroll
-      for (int u = 0; u < kGroup; ++u) {
-        const int j = j0 + u;
-        const float2 gm = s_xy[j];
-        const float4 gc = s_co[j];
-        const float4 cc = s_rgb[j];
-        const float gz = kCh ? s_z[j] : 0.0f;
-        const float4 gv = kCh ? s_fv[j] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        const int pos = __float_as_int(cc.w);
-        const float dx = gm.x - fpx;
-        const float c1 = gc.y * dx, c0 = (gc.x * dx) * dx;
+          for (int k = 0; k < kPx; ++k) Tn[k] = T[k];
 #pragma unroll
-        for (int k = 0; k < kPix; ++k) {
-          if (kCount) evaluated += (act[k] && j < cnt) ? 1 : 0;
-          const float dy = gm.y - static_cast<float>(py0 + 4 * k);
-          const float p2 = pair_exp2(gc.z, c1, c0, dy);
-          const float alpha = fminf(kAlphaMax, gc.w * __builtin_amdgcn_exp2f(p2));
-          const bool ok = act[k] && !(p2 > 0.0f) && !(alpha < kAlphaMin);
-          const float Tn = T[k] * (1.0f - alpha);
-          const bool stop = ok && Tn < kTMin;
-          const bool use = ok && !stop;
-          const float w = use ? alpha * T[k] : 0.0f;
-          Cr[k] = fmaf(cc.x, w, Cr[k]);
-          Cg[k] = fmaf(cc.y, w, Cg[k]);
-          Cb[k] = fmaf(cc.z, w, Cb[k]);
-          if (kCh) {
-            Dz[k] = fmaf(gz, w, Dz[k]);
-            Aw[k] += w;
-            V0[k] = fmaf(gv.x, w, V0[k]);
-            V1[k] = fmaf(gv.y, w, V1[k]);
-            V2[k] = fmaf(gv.z, w, V2[k]);
-            Rh[k] = fmaf(gv.w, w, Rh[k]);
+          for (int u = 0; u < kGroup; ++u) {
+            const float2 gm = s_xy[j0 + u];
+            const float4 gc = s_co[j0 + u];
+            const float dx = gm.x - fpx;
+            const float c1 = gc.y * dx, c0 = (gc.x * dx) * dx;
+#pragma unroll
+            for (int k = 0; k < kPx; ++k) {
+              const float dy = gm.y - static_cast<float>(py0 + 4 * k);
+              const float p2 = pair_exp2(gc.z, c1, c0, dy);
+              const float raw = gc.w * __builtin_amdgcn_exp2f(p2);
+              const float alpha = kPlain ? raw : fminf(kAlphaMax, raw);
+              ok[u][k] = !(alpha < thr[k]) && (kPlain || !(p2 > 0.0f));
+              const float au = ok[u][k] ? alpha : 0.0f;
+              w[u][k] = au * Tn[k];
+              Tn[k] = Tn[k] * (1.0f - au);
+            }
           }
-          T[k] = use ? Tn : T[k];
-          last[k] = use ? pos : last[k];
-          act[k] = act[k] && !stop;
+          bool stops = false;
+#pragma unroll
+          for (int k = 0; k < kPx; ++k) stops = stops || Tn[k] < kTMin;
+          if (__any(stops)) {
+            stopped = true;
+            break;
+          }
+#pragma unroll
+          for (int u = 0; u < kGroup; ++u) {
+            const float4 cc = s_rgb[j0 + u];
+            const float gz = kCh ? s_z[j0 + u] : 0.0f;
+            const float4 gv = kCh ? s_fv[j0 + u] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            const int pos = kTest ? __float_as_int(cc.w) : static_cast<int>(b0 - start) + j0 + u + 1;
+#pragma unroll
+            for (int k = 0; k < kPx; ++k) {
+              if (kCount) evaluated += (thr[k] < 1.0f && j0 + u < cnt) ? 1 : 0;
+              blend(k, cc, gz, gv, w[u][k]);
+              last[k] = ok[u][k] ? pos : last[k];
+            }
+          }
+#pragma unroll
+          for (int k = 0; k < kPx; ++k) T[k] = Tn[k];
         }
+        if (!stopped) return;
+#pragma unroll 1
+        for (int j = j0; j < j0 + kGroup; ++j) {
+          const float2 gm = s_xy[j];
+          const float4 gc = s_co[j];
+          const float4 cc = s_rgb[j];
+          const float gz = kCh ? s_z[j] : 0.0f;
+          const float4 gv = kCh ? s_fv[j] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          const int pos = kTest ? __float_as_int(cc.w) : static_cast<int>(b0 - start) + j + 1;
+          const float dx = gm.x - fpx;
+          const float c1 = gc.y * dx, c0 = (gc.x * dx) * dx;
+          bool on = false;
+#pragma unroll
+          for (int k = 0; k < kPx; ++k) {
+            if (kCount) evaluated += (thr[k] < 1.0f && j < cnt) ? 1 : 0;
+            const float dy = gm.y - static_cast<float>(py0 + 4 * k);
+            const float p2 = pair_exp2(gc.z, c1, c0, dy);
+            const float raw = gc.w * __builtin_amdgcn_exp2f(p2);
+            const float alpha = kPlain ? raw : fminf(kAlphaMax, raw);
+            const bool pass = !(alpha < thr[k]) && (kPlain || !(p2 > 0.0f));
+            const float Tp = T[k] * (1.0f - alpha);
+            const bool stop = pass && Tp < kTMin, use = pass && !stop;
+            blend(k, cc, gz, gv, use ? alpha * T[k] : 0.0f);
+            T[k] = use ? Tp : T[k];
+            last[k] = use ? pos : last[k];
+            thr[k] = stop ? kNever : thr[k];
+            on = on || thr[k] < 1.0f;
+          }
+          live = __ballot(on);
+        }
+        if (!live) return;
       }
-    }
+    };
+    if (__all(plain)) walk(std::true_type{});
+    else walk(std::false_type{});
     __syncthreads();
   }
   const int64_t HW = static_cast<int64_t>(v.W) * v.H;
 #pragma unroll
-  for (int k = 0; k < kPix; ++k) {
+  for (int k = 0; k < kPx; ++k) {
     const int py = py0 + 4 * k;
     if (px < v.W && py < v.H) {
       const int64_t o = static_cast<int64_t>(py) * v.W + px;
@@ -520,14 +611,20 @@ hipError_t launch_render_fwd(const ViewSet& vs, const Geom& geom, const uint32_t
                              bool culled, hipStream_t s) {
   if (vs.total_tiles == 0) return hipSuccess;
   StageScope scope(PVG_STAGE_RENDER_FWD, s);
-  const dim3 grid(static_cast<unsigned>(render_grid(vs.total_tiles)));
+  const int parts = forward_parts(vs.total_tiles);
+  const dim3 grid(static_cast<unsigned>(parts * render_grid(vs.total_tiles)));
   unsigned long long* cnt = profile_work_counter(PVG_STAGE_RENDER_FWD);
   // channels are single-view only
-  const bool depth = !vs.table && (vs.one.depth_img || vs.one.vbar_img || vs.one.rho_img);
-  auto k = depth ? (cnt ? (culled ? k_render_fwd<true, true, true> : k_render_fwd<true, false, true>)
-                        : (culled ? k_render_fwd<false, true, true> : k_render_fwd<false, false, true>))
-                 : (cnt ? (culled ? k_render_fwd<true, true, false> : k_render_fwd<true, false, false>)
-                        : (culled ? k_render_fwd<false, true, false> : k_render_fwd<false, false, false>));
+  const bool ch = !vs.table && (vs.one.depth_img || vs.one.vbar_img || vs.one.rho_img);
+  auto pick = [&](auto count, auto channels) {
+    constexpr bool kCount = decltype(count)::value, kCh = decltype(channels)::value;
+    return parts == 4 ? k_render_fwd<kCount, true, kCh, 1>
+           : parts == 2 ? k_render_fwd<kCount, true, kCh, 2>
+           : culled ? k_render_fwd<kCount, false, kCh, 4> : k_render_fwd<kCount, true, kCh, 4>;
+  };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  auto k = ch ? (cnt ? pick(yes, yes) : pick(no, yes)) : (cnt ? pick(yes, no) : pick(no, no));
   hipLaunchKernelGGL(k, grid, dim3(64), 0, s, vs, geom, vals, ranges, cnt);
   return hipGetLastError();
 }
