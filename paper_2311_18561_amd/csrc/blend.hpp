@@ -129,6 +129,36 @@ __device__ __forceinline__ void wave_sum_store(const float* a, int lane, float* 
   }
 }
 
+// Wave totals of kN sums of four pairs at once: h[q][0] holds sum q of pairs
+// 0 | 1 and h[q][1] of pairs 2 | 3, each already folded over the half-waves by
+// swap_sum32.  A row swap leaves pairs 0, 2, 1, 3 in rows 0 .. 3, 16 lanes
+// each; those go through LDS (red: 4 kN rows of kRedStride floats, 16-byte
+// aligned), where one lane per (sum, pair) adds its 16 in the order of the
+// DPP form's folds (lane ^ 8, ^ 4, ^ 2, ^ 1).  dst[kN u + q] receives sum q of
+// pair u.  Per pair the fold costs 2.25 kN / 3 swaps, as many adds and four
+// adds, where wave_sum10 / wave_sum16 take a DPP add per value and step.
+constexpr int kRedStride = 20;  // floats between rows: 16 used, and the readers' 16-byte reads fall on distinct banks
+template <int kN>
+__device__ __forceinline__ void group_sum_store(const float (&h)[kN][2], int lane, float* red, float* dst) {
+  const int row = lane >> 4;
+#pragma unroll
+  for (int q = 0; q < kN; ++q) red[(4 * q + row) * kRedStride + (lane & 15)] = swap_sum16(h[q][0], h[q][1]);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  if (lane < 4 * kN) {
+    const float4* r = reinterpret_cast<const float4*>(red + lane * kRedStride);
+    const float4 a = r[0], b = r[1], c = r[2], d = r[3];
+    const float4 e = make_float4((a.x + c.x) + (b.x + d.x), (a.y + c.y) + (b.y + d.y), (a.z + c.z) + (b.z + d.z),
+                                 (a.w + c.w) + (b.w + d.w));
+    const int u = 2 * (lane & 1) + ((lane >> 1) & 1);  // the pair in row lane mod 4
+    dst[kN * u + (lane >> 2)] = (e.x + e.z) + (e.y + e.w);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ int wave_max(int x) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) x = max(x, __shfl_xor(x, off, 64));

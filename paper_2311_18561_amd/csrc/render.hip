@@ -11,8 +11,8 @@
 //
 // The adjoint walks the list backwards from the wave's last contributor,
 // recovering each pixel's transmittance by division, sums the four pixels'
-// screen-space gradients per lane and reduces them across the wave.  Each
-// (Gaussian, tile) pair's nine sums are stored, without atomics, at the pair's
+// screen-space gradients per lane and reduces them across the wave, four
+// pairs at a time.  Each (Gaussian, tile) pair's nine sums are stored, without atomics, at the pair's
 // index in emission order (a Gaussian's pairs are contiguous there) and
 // flagged in a byte array; a gather kernel then adds each Gaussian's flagged
 // pairs.  Device-scope float atomics resolve
@@ -22,6 +22,7 @@
 // Tiles reach the eight XCDs in row-sized chunks dealt round-robin
 // (xcd_tile), which balances the XCDs' work and keeps a chunk's shared
 // Gaussians in one L2.
+#include <climits>
 #include <type_traits>
 
 #include "blend.hpp"
@@ -280,8 +281,25 @@ __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const 
 // kCh: the view also carries upstream gradients of the depth, velocity and
 // staticness channels and/or of final_T (each may be null); records then hold
 // five more sums (d z, d v~, d rho).
+//
+// Bound: vector issue (a 1M-Gaussian 1920x1280 view walks 1.2M pairs of 256
+// pixels; its records are 60 MB).  Four pairs form a group: their pixel work
+// is unrolled back to front, and their 36 (56) sums are folded together
+// (group_sum_store), which takes a third of the instructions of folding each
+// pair's nine by DPP.  A batch whose pairs cannot clamp (pair_is_plain) walks
+// without the clamp's tests, a group behind every pixel's last contributor
+// without the position's.  Per view, us: 1M 386 -> 310 (channels 491 -> 463),
+// 200k at 960x640 163 -> 136.  Three waves a SIMD (141 registers; channels
+// 168): plain at four 313 and at five, which spills, 333; channels at two 488.
+//
+// The order of every sum is fixed by design, pair by pair and pixel by pixel:
+// near the camera a Gaussian's gradient is the difference of sums many
+// thousand times its size, so another order moves single elements by more
+// than 1e-3 of their size.  The two products of the mean's gradient are
+// written as fused multiply-adds for the same reason: left to contraction,
+// which product is rounded first depends on the instantiation.
 template <bool kCount, bool kCulled, bool kCh>
-__global__ void __launch_bounds__(64) k_render_bwd(ViewSet vs, Geom geom, Lists lists, float* rec,
+__global__ void __launch_bounds__(64, 3) k_render_bwd(ViewSet vs, Geom geom, Lists lists, float* rec,
                                                    uint8_t* vis, unsigned long long* pair_counter) {
   // The gradient arithmetic may fuse multiply-adds.  Every branch decision
   // (exponent sign, alpha thresholds) comes from pair_coefs, pair_exp2 (its
@@ -290,16 +308,16 @@ __global__ void __launch_bounds__(64) k_render_bwd(ViewSet vs, Geom geom, Lists 
 #pragma clang fp contract(fast)
   const uint32_t* __restrict__ vals = lists.vals;
   const uint32_t* __restrict__ ranges = lists.ranges;
+  constexpr int kG = 4;                 // pairs per group
+  constexpr int kSums = kCh ? 14 : 9;   // also the record stride
   __shared__ float2 s_xy[64];
   __shared__ float4 s_co[64];   // -A, -B, -C and 1 / o
   __shared__ float4 s_q[64];    // pair_coefs of the conic and the opacity
   __shared__ float4 s_rgb[64];  // rgb and the 0-based list position (as int bits)
-  __shared__ uint32_t s_g[64];
-  __shared__ float s_acc[64][kRecFloats];
   __shared__ float s_z[kCh ? 64 : 1];
   __shared__ float4 s_fv[kCh ? 64 : 1];
-  __shared__ int s_any[64];
-  constexpr int kSums = kCh ? 14 : 9;  // also the record stride
+  __shared__ __align__(16) float s_red[kSums * kG * kRedStride];
+  __shared__ float s_acc[64][kSums];
   const int64_t ntiles = live_tiles(vs);
   const int64_t tile = xcd_tile(blockIdx.x, vs.total_tiles);
   if (tile >= ntiles) return;
@@ -317,16 +335,20 @@ __global__ void __launch_bounds__(64) k_render_bwd(ViewSet vs, Geom geom, Lists 
   float T[kPix], rr[kPix], gr[kPix], gg[kPix], gb[kPix];
   float gd[kPix], gv0[kPix], gv1[kPix], gv2[kPix], gh[kPix];  // channel gradients: z, v~, rho
   int last[kPix];
-  int lmax = 0;
+  float thr[kPix];  // alpha a pair needs to be used: 1/255, or infinity outside the image
+  int lmax = 0, lmin = INT_MAX;
 #pragma unroll
   for (int k = 0; k < kPix; ++k) {
     const int py = py0 + 4 * k;
     float gt = 0.0f;
     gd[k] = 0.0f; gv0[k] = 0.0f; gv1[k] = 0.0f; gv2[k] = 0.0f; gh[k] = 0.0f;
+    thr[k] = kNever;
     if (px < v.W && py < v.H) {
       const int64_t o = static_cast<int64_t>(py) * v.W + px;
+      thr[k] = kAlphaMin;
       T[k] = v.final_T[o];
       last[k] = v.n_contrib[o];
+      lmin = min(lmin, last[k]);
       gr[k] = v.dL_dimg[o];
       gg[k] = v.dL_dimg[HW + o];
       gb[k] = v.dL_dimg[2 * HW + o];
@@ -360,12 +382,13 @@ __global__ void __launch_bounds__(64) k_render_bwd(ViewSet vs, Geom geom, Lists 
     lmax = max(lmax, last[k]);
   }
   lmax = wave_max(lmax);
+  lmin = -wave_max(-lmin);
   const uint32_t start = ranges[2 * tile];
   lmax = min(lmax, static_cast<int>(ranges[2 * tile + 1] - start));  // never read past the tile's list
   long long evaluated = 0;
   for (int hi = lmax; hi > 0; hi -= 64) {
     const int lo = max(0, hi - 64);
-    bool keep = false;
+    bool keep = false, plain = true;
     uint32_t g = 0;
     float2 m;
     float4 co, c;
@@ -381,11 +404,12 @@ __global__ void __launch_bounds__(64) k_render_bwd(ViewSet vs, Geom geom, Lists 
         if (geom.feat) fv = reinterpret_cast<const float4*>(geom.feat)[g];
       }
       keep = kCulled || tile_reachable(m.x, m.y, co.x, co.y, co.z, co.w, X0, X1, Y0, Y1);
+      plain = !keep || pair_is_plain(m, co);
     }
     const uint64_t km = __ballot(keep);
+    const int cnt = __popcll(km);
+    const int slot = __popcll(km & lt);
     if (keep) {
-      const int slot = __popcll(km & lt);
-      s_g[slot] = g;
       s_xy[slot] = m;
       // the negated conic and 1 / o for the record sums (one reciprocal per
       // Gaussian and batch rather than per pair)
@@ -397,123 +421,132 @@ __global__ void __launch_bounds__(64) k_render_bwd(ViewSet vs, Geom geom, Lists 
         s_fv[slot] = fv;
       }
     }
-    __syncthreads();
-    const int cnt = __popcll(km);
-    for (int j = cnt - 1; j >= 0; --j) {
-      const float2 gm = s_xy[j];
-      const float4 gc = s_co[j];
-      const float4 gq = s_q[j];
-      const float4 cc = s_rgb[j];
-      const float gz = kCh ? s_z[j] : 0.0f;
-      const float4 gf = kCh ? s_fv[j] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      const int pos = __float_as_int(cc.w);
-      // The lane's four pixels share the column offset dx.  Per pixel the
-      // power gradient is gp = alpha dL/dalpha (zero where the pair is unused
-      // or alpha is clamped); the lane sums s0 = sum gp, s1 = sum gp dy and
-      // s2 = sum gp dy^2, from which the moments of gp in (dx, dy) follow.
-      // An unused pair takes alpha = 0, which leaves T (rcp(1) is exact)
-      // and the colour behind it unchanged, so no selects are needed.
-      const float dx = gm.x - fpx;
-      const float c1 = gq.y * dx, c0 = (gq.x * dx) * dx;
-      float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, cr = 0.0f, cgr = 0.0f, cb = 0.0f;
-      float cz = 0.0f, cv0 = 0.0f, cv1 = 0.0f, cv2 = 0.0f, ch = 0.0f;
-      bool any = false;
-#pragma unroll
-      for (int k = 0; k < kPix; ++k) {
-        const bool inr = pos < last[k];
-        if (kCount) evaluated += inr ? 1 : 0;
-        const float dy = gm.y - static_cast<float>(py0 + 4 * k);
-        const float p2 = pair_exp2(gq.z, c1, c0, dy);
-        const float raw = gq.w * __builtin_amdgcn_exp2f(p2);
-        const float alpha = fminf(kAlphaMax, raw);
-        const bool ok = inr && !(p2 > 0.0f) && !(alpha < kAlphaMin);
-        any = any || ok;
-        const float au = ok ? alpha : 0.0f;
-        const float om = 1.0f - au;
-        T[k] *= __builtin_amdgcn_rcpf(om);
-        float cg = cc.x * gr[k] + cc.y * gg[k] + cc.z * gb[k];
-        if (kCh) {  // the channels blend like a colour
-          cg = fmaf(gz, gd[k], cg);
-          cg = fmaf(gf.x, gv0[k], cg);
-          cg = fmaf(gf.y, gv1[k], cg);
-          cg = fmaf(gf.z, gv2[k], cg);
-          cg = fmaf(gf.w, gh[k], cg);
-        }
-        const float d = cg - rr[k];
-        const float dal = T[k] * d;
-        const float w = au * T[k];
-        cr = fmaf(w, gr[k], cr);
-        cgr = fmaf(w, gg[k], cgr);
-        cb = fmaf(w, gb[k], cb);
-        if (kCh) {
-          cz = fmaf(w, gd[k], cz);
-          cv0 = fmaf(w, gv0[k], cv0);
-          cv1 = fmaf(w, gv1[k], cv1);
-          cv2 = fmaf(w, gv2[k], cv2);
-          ch = fmaf(w, gh[k], ch);
-        }
-        rr[k] = fmaf(au, d, rr[k]);  // alpha c + (1 - alpha) rr
-        const float gp = (raw > kAlphaMax ? 0.0f : au) * dal;
-        s0 += gp;
-        s1 = fmaf(dy, gp, s1);
-        s2 = fmaf(dy * dy, gp, s2);
+    if (lane >= cnt && lane < (cnt + kG - 1) / kG * kG) {  // padding pairs, which no pixel uses
+      s_xy[lane] = make_float2(0.0f, 0.0f);
+      s_co[lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      s_q[lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      s_rgb[lane] = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(INT_MAX));
+      if (kCh) {
+        s_z[lane] = 0.0f;
+        s_fv[lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
       }
-      // power = -(A dx^2 + C dy^2)/2 - B dx dy and d(mean) = d(dx, dy); the
-      // exponential's own gradient, sum G dL/dalpha over unclamped pairs, is
-      // s0 / o (there alpha = o G)
-      float a[16];
-      {
-        const float sx = dx * s0;
-        a[0] = gc.x * sx + gc.y * s1;  // gc holds -A, -B, -C
-        a[1] = gc.y * sx + gc.z * s1;
-        a[2] = -0.5f * (dx * sx);
-        a[3] = -(dx * s1);
-        a[4] = -0.5f * s2;
-        a[5] = s0 * gc.w;  // gc.w = 1 / o (0 for o = 0)
-        a[6] = cr;
-        a[7] = cgr;
-        a[8] = cb;
-        a[9] = cz;  // the channel sums are 0 without channels
-        a[10] = cv0;
-        a[11] = cv1;
-        a[12] = cv2;
-        a[13] = ch;
-        a[14] = 0.0f;
-        a[15] = 0.0f;
-      }
-      const bool wany = __any(any);
-      if (wany) {
-        if (kCh) {
-          float red[4];
-          wave_sum16(a, red);
-          if ((lane & 15) == 0) {
-            const int r = lane >> 4;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const int q = 4 * k + 2 * (r & 1) + (r >> 1);
-              if (q < kSums) s_acc[j][q] = red[k];
-            }
-          }
-        } else {
-          float red[3];
-          wave_sum10(a, red);
-          if ((lane & 15) == 0) {
-            const int r = lane >> 4;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-              const int q = 4 * k + 2 * (r & 1) + (r >> 1);
-              if (q < kSums) s_acc[j][q] = red[k];
-            }
-          }
-        }
-      }
-      if (lane == 0) s_any[j] = wany ? 1 : 0;
     }
     __syncthreads();
-    if (keep && s_any[__popcll(km & lt)] != 0) {
+    uint64_t used = 0;  // pairs of the batch that some pixel uses
+    // One group of pairs j0 .. j0 + 3.  kPlain: no pair of the batch needs the
+    // clamp or the exponent's sign; kAll: every pixel is past its last
+    // contributor's position, so the list position needs no test.
+    auto group = [&](auto plain_pairs, auto all_pixels, int j0) {
+      constexpr bool kPlain = decltype(plain_pairs)::value, kAll = decltype(all_pixels)::value;
+      float h[kSums][2];  // the pairs' sums folded over the half-waves: pairs 0 | 1 and 2 | 3
+#pragma unroll
+      for (int half = 1; half >= 0; --half) {
+        float a[2][kSums];
+#pragma unroll
+        for (int sub = 1; sub >= 0; --sub) {
+          const int u = 2 * half + sub, j = j0 + u;
+          const float2 gm = s_xy[j];
+          const float4 gc = s_co[j];
+          const float4 gq = s_q[j];
+          const float4 cc = s_rgb[j];
+          const float gz = kCh ? s_z[j] : 0.0f;
+          const float4 gf = kCh ? s_fv[j] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          const int pos = __float_as_int(cc.w);
+          // The lane's four pixels share the column offset dx.  Per pixel the
+          // power gradient is gp = alpha dL/dalpha (zero where the pair is unused
+          // or alpha is clamped); the lane sums s0 = sum gp, s1 = sum gp dy and
+          // s2 = sum gp dy^2, from which the moments of gp in (dx, dy) follow.
+          // An unused pair takes alpha = 0, which leaves T (rcp(1) is exact)
+          // and the colour behind it unchanged, so no selects are needed.
+          const float dx = gm.x - fpx;
+          const float c1 = gq.y * dx, c0 = (gq.x * dx) * dx;
+          float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, cr = 0.0f, cgr = 0.0f, cb = 0.0f;
+          float cz = 0.0f, cv0 = 0.0f, cv1 = 0.0f, cv2 = 0.0f, ch = 0.0f;
+          uint64_t any = 0;
+#pragma unroll
+          for (int k = 0; k < kPix; ++k) {
+            if (kCount) evaluated += (thr[k] < 1.0f && j < cnt && (kAll || pos < last[k])) ? 1 : 0;
+            const float dy = gm.y - static_cast<float>(py0 + 4 * k);
+            const float p2 = pair_exp2(gq.z, c1, c0, dy);
+            const float raw = gq.w * __builtin_amdgcn_exp2f(p2);
+            const float alpha = kPlain ? raw : fminf(kAlphaMax, raw);
+            bool ok = !(alpha < thr[k]);
+            if (!kPlain) ok = ok && !(p2 > 0.0f);
+            if (!kAll) ok = ok && pos < last[k];
+            any |= __ballot(ok);
+            const float au = ok ? alpha : 0.0f;
+            const float om = 1.0f - au;
+            T[k] *= __builtin_amdgcn_rcpf(om);
+            float cg = cc.x * gr[k] + cc.y * gg[k] + cc.z * gb[k];
+            if (kCh) {  // the channels blend like a colour
+              cg = fmaf(gz, gd[k], cg);
+              cg = fmaf(gf.x, gv0[k], cg);
+              cg = fmaf(gf.y, gv1[k], cg);
+              cg = fmaf(gf.z, gv2[k], cg);
+              cg = fmaf(gf.w, gh[k], cg);
+            }
+            const float d = cg - rr[k];
+            const float dal = T[k] * d;
+            const float w = au * T[k];
+            cr = fmaf(w, gr[k], cr);
+            cgr = fmaf(w, gg[k], cgr);
+            cb = fmaf(w, gb[k], cb);
+            if (kCh) {
+              cz = fmaf(w, gd[k], cz);
+              cv0 = fmaf(w, gv0[k], cv0);
+              cv1 = fmaf(w, gv1[k], cv1);
+              cv2 = fmaf(w, gv2[k], cv2);
+              ch = fmaf(w, gh[k], ch);
+            }
+            rr[k] = fmaf(au, d, rr[k]);  // alpha c + (1 - alpha) rr
+            const float gp = (!kPlain && raw > kAlphaMax ? 0.0f : au) * dal;
+            s0 += gp;
+            s1 = fmaf(dy, gp, s1);
+            s2 = fmaf(dy * dy, gp, s2);
+          }
+          used |= any ? 1ull << j : 0ull;
+          // power = -(A dx^2 + C dy^2)/2 - B dx dy and d(mean) = d(dx, dy); the
+          // exponential's own gradient, sum G dL/dalpha over unclamped pairs, is
+          // s0 / o (there alpha = o G)
+          const float sx = dx * s0;
+          a[sub][0] = kCh ? fmaf(gc.x, sx, gc.y * s1) : fmaf(gc.y, s1, gc.x * sx);
+          a[sub][1] = kCh ? fmaf(gc.y, sx, gc.z * s1) : fmaf(gc.z, s1, gc.y * sx);
+          a[sub][2] = -0.5f * (dx * sx);
+          a[sub][3] = -(dx * s1);
+          a[sub][4] = -0.5f * s2;
+          a[sub][5] = s0 * gc.w;  // gc.w = 1 / o (0 for o = 0)
+          a[sub][6] = cr;
+          a[sub][7] = cgr;
+          a[sub][8] = cb;
+          if constexpr (kCh) {
+            a[sub][9] = cz;
+            a[sub][10] = cv0;
+            a[sub][11] = cv1;
+            a[sub][12] = cv2;
+            a[sub][13] = ch;
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) h[q][half] = swap_sum32(a[0][q], a[1][q]);
+      }
+      group_sum_store<kSums>(h, lane, s_red, &s_acc[j0][0]);
+    };
+    auto walk = [&](auto plain_pairs) {
+      int j0 = (cnt - 1) / kG * kG;
+      if (cnt == 0) return;
+      for (; j0 >= 0; j0 -= kG) {  // until every pixel is past its last contributor
+        const int p_hi = __builtin_amdgcn_readfirstlane(__float_as_int(s_rgb[j0 + kG - 1].w));
+        if (p_hi < lmin) break;  // (a padding pair's position is never below)
+        group(plain_pairs, std::false_type{}, j0);
+      }
+      for (; j0 >= 0; j0 -= kG) group(plain_pairs, std::true_type{}, j0);
+    };
+    if (__all(plain)) walk(std::true_type{});
+    else walk(std::false_type{});
+    __syncthreads();
+    if (keep && (used >> slot & 1ull)) {
       // record of this (Gaussian, tile) pair at its emission-order index,
       // flagged for the gather (pairs no pixel used keep flag 0, no record)
-      const int slot = __popcll(km & lt);
       const uint32_t e = record_index<kCulled>(lists, geom, v, g, m, tx, ty);
       if (static_cast<int64_t>(e) < lists.capacity) {
         float* dst = rec + kSums * static_cast<int64_t>(e);
