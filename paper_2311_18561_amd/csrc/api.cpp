@@ -174,6 +174,8 @@ static ViewSet single(const View& v, int64_t n) {
   vs.nviews = 1;
   vs.total_gauss = n;
   vs.total_tiles = static_cast<int64_t>(v.GX) * v.GY;
+  vs.total_rows = v.GY;
+  vs.max_cols = v.GX;
   return vs;
 }
 

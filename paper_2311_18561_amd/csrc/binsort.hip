@@ -18,10 +18,16 @@
 // With tile culling on, step 3 lists a Gaussian only in the tiles it can
 // reach (alpha >= 1/255 at some pixel).  Those form one column interval per
 // tile row of its rectangle, so the culled emission works on rows: count the
-// rectangle rows, compute every row's interval once (a thread per Gaussian,
-// at most one loop over its rows), scan the interval lengths into instance
-// offsets and write each row's interval (a thread per row).  Fewer instances
-// then reach the tile sort, the ranges and the compositing loops.
+// rectangle rows, compute every row's interval once, scan the interval
+// lengths into instance offsets.  Fewer instances then reach the lists and
+// the compositing loops, and since a row's instances are consecutive tiles of
+// one tile row, steps 3 to 5 become a sort of the rows by tile row and one
+// expansion that writes the finished lists and ranges (k_row_keys to
+// k_row_expand).  Per view: 1M Gaussians at 1920x1280 (5 to 11M instances)
+// 200 -> 106 us, 6M (20 to 70M) 640 -> 285, 200k at 960x640 (3.5M) 130 -> 78;
+// eight served views of three sizes 1,935 -> 1,573 us in all.  Launches whose
+// widths or rows the packed records cannot hold, and capacities too small for
+// the tables, emit instances row by row (a thread per row) and sort them.
 //
 // Every radix pass is the classic three-kernel form: per-block digit
 // histograms in LDS (atomics on LDS counters), an exclusive scan of each
@@ -62,25 +68,26 @@ __device__ __forceinline__ T wave_incl_scan(T x, int lane) {
   return x;
 }
 
-// Exclusive scan of one value per thread over a 256-thread block.
-template <class T>
-__device__ __forceinline__ T block_excl_scan(T v, T* lds5, T& total) {
+// Exclusive scan of one value per thread over a block of kN threads (lds:
+// kN / 64 + 1 values).
+template <class T, int kN = kThreads>
+__device__ __forceinline__ T block_excl_scan(T v, T* lds, T& total) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const T x = wave_incl_scan<T>(v, lane);
-  if (lane == 63) lds5[wid] = x;
+  if (lane == 63) lds[wid] = x;
   __syncthreads();
   if (tid == 0) {
     T s = 0;
-    for (int w = 0; w < kThreads / 64; ++w) {
-      const T t = lds5[w];
-      lds5[w] = s;
+    for (int w = 0; w < kN / 64; ++w) {
+      const T t = lds[w];
+      lds[w] = s;
       s += t;
     }
-    lds5[4] = s;
+    lds[kN / 64] = s;
   }
   __syncthreads();
-  const T r = lds5[wid] + x - v;
-  total = lds5[4];
+  const T r = lds[wid] + x - v;
+  total = lds[kN / 64];
   __syncthreads();
   return r;
 }
@@ -108,19 +115,13 @@ __global__ void __launch_bounds__(kThreads) k_vis_count(const uint32_t* __restri
   if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
 
-// Exclusive scan of `count` block partials in place (one block), unless
-// *skip is set.  The total goes to *total_out; with cap >= 0 it is checked
-// against the capacity: over it, *total_out = 0 and *over_flag = 1.
-// sat_out (optional) receives the total saturated to 32 bits.
-__global__ void __launch_bounds__(1024) k_scan_partials(unsigned long long* partials, const uint32_t* count_dev,
-                                                        const int64_t* count_dev64, int64_t count_host,
-                                                        int per_block, uint32_t* total_out, int64_t cap,
-                                                        uint32_t* over_flag, uint32_t* sat_out,
-                                                        const uint32_t* skip) {
-  __shared__ unsigned long long wsum[17];
-  if (skip && *skip) return;
-  const int64_t items = count_dev64 ? *count_dev64 : live_count(count_dev, count_host);
-  const int64_t count = (items + per_block - 1) / per_block;
+// Exclusive scan of `count` block partials in place (one block of 1024).  The
+// total goes to *total_out; with cap >= 0 it is checked against the capacity:
+// over it, *total_out = 0 and *over_flag = 1.  sat_out (optional) receives the
+// total saturated to 32 bits.
+__device__ __forceinline__ void scan_partials_block(unsigned long long* partials, int64_t count,
+                                                    unsigned long long* wsum, uint32_t* total_out, int64_t cap,
+                                                    uint32_t* over_flag, uint32_t* sat_out) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   unsigned long long carry = 0;
   for (int64_t base = 0; base < count; base += 1024) {
@@ -149,6 +150,18 @@ __global__ void __launch_bounds__(1024) k_scan_partials(unsigned long long* part
     if (over) *over_flag = 1u;
     if (sat_out) *sat_out = carry > 0xffffffffull ? 0xffffffffu : static_cast<uint32_t>(carry);
   }
+}
+// scan_partials_block over the blocks of `per_block` items each, unless *skip
+// is set.
+__global__ void __launch_bounds__(1024) k_scan_partials(unsigned long long* partials, const uint32_t* count_dev,
+                                                        const int64_t* count_dev64, int64_t count_host,
+                                                        int per_block, uint32_t* total_out, int64_t cap,
+                                                        uint32_t* over_flag, uint32_t* sat_out,
+                                                        const uint32_t* skip) {
+  __shared__ unsigned long long wsum[17];
+  if (skip && *skip) return;
+  const int64_t items = count_dev64 ? *count_dev64 : live_count(count_dev, count_host);
+  scan_partials_block(partials, (items + per_block - 1) / per_block, wsum, total_out, cap, over_flag, sat_out);
 }
 
 __global__ void __launch_bounds__(kThreads) k_vis_compact(const uint32_t* __restrict__ tiles,
@@ -237,12 +250,86 @@ __global__ void __launch_bounds__(kThreads) k_rs_rowscan(uint32_t* hist, int64_t
   if (threadIdx.x == 0) rowtot[blockIdx.x] = carry;
 }
 
-// Scatter of one stable LSD pass.  Each wave ranks its own contiguous 1024
-// keys (wave ballots find lanes with equal digits; a wave-private LDS counter
-// per digit carries ranks across its 16 sub-tiles), the block combines the
-// four waves per digit, stages the block's 4096 pairs locally sorted in LDS and
-// writes each digit's run contiguously.  A thread owns kPerT consecutive
-// digits in the block-wide digit scans.
+// Rank of the lane's digit among those its wave has passed here so far, in
+// lane order: wave ballots find the lanes with equal digits and cnt[digit]
+// (wave-private, in LDS) carries the count across calls.  Lanes that are not
+// `valid` take no part and get 0xffffffff.
+__device__ __forceinline__ uint32_t wave_rank(uint32_t dig, bool valid, int bits, uint32_t* cnt, uint64_t lt) {
+  uint64_t peers = __ballot(valid);
+  for (int b = 0; b < bits; ++b) {
+    const bool bit = (dig >> b) & 1u;
+    const uint64_t bal = __ballot(bit);
+    peers &= bit ? bal : ~bal;
+  }
+  uint32_t old = 0;
+  if (valid) old = cnt[dig];
+  const uint32_t rank = old + static_cast<uint32_t>(__popcll(peers & lt));
+  __builtin_amdgcn_wave_barrier();
+  if (valid && (peers & lt) == 0) cnt[dig] = old + static_cast<uint32_t>(__popcll(peers));
+  __builtin_amdgcn_wave_barrier();
+  return valid ? rank : 0xffffffffu;
+}
+
+// From the four waves' digit counts s_cnt (fewer than 2^kMaxBits digits
+// used): s_off[d] becomes the block's first slot of digit d, s_cnt[w][d] wave
+// w's.  tot[j] is the count of digit tid * kPerT + j.
+template <int kR, int kPerT>
+__device__ __forceinline__ void combine_digits(uint32_t (*s_cnt)[kR], uint32_t* s_off, int radix, uint32_t* lds,
+                                               uint32_t (&tot)[kPerT]) {
+  const int tid = threadIdx.x;
+  uint32_t c[kPerT][kThreads / 64], sum = 0;
+#pragma unroll
+  for (int j = 0; j < kPerT; ++j) {
+    const int d = tid * kPerT + j;
+    tot[j] = 0;
+    for (int w = 0; w < kThreads / 64; ++w) {
+      c[j][w] = d < radix ? s_cnt[w][d] : 0u;
+      tot[j] += c[j][w];
+    }
+    sum += tot[j];
+  }
+  uint32_t all;
+  uint32_t off = block_excl_scan<uint32_t>(sum, lds, all);
+#pragma unroll
+  for (int j = 0; j < kPerT; ++j) {
+    const int d = tid * kPerT + j;
+    if (d < radix) {
+      s_off[d] = off;
+      uint32_t run = off;
+      for (int w = 0; w < kThreads / 64; ++w) {
+        s_cnt[w][d] = run;
+        run += c[j][w];
+      }
+    }
+    off += tot[j];
+  }
+}
+
+// Exclusive scan of the digits' totals: base[j] of digit tid * kPerT + j.
+template <int kPerT>
+__device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rowtot, int radix, uint32_t* lds,
+                                            uint32_t (&base)[kPerT]) {
+  uint32_t t[kPerT], sum = 0;
+#pragma unroll
+  for (int j = 0; j < kPerT; ++j) {
+    const int d = threadIdx.x * kPerT + j;
+    t[j] = d < radix ? rowtot[d] : 0u;
+    sum += t[j];
+  }
+  uint32_t tot;
+  uint32_t run = block_excl_scan<uint32_t>(sum, lds, tot);
+#pragma unroll
+  for (int j = 0; j < kPerT; ++j) {
+    base[j] = run;
+    run += t[j];
+  }
+}
+
+// Scatter of one stable LSD pass.  Each wave ranks its own contiguous 64 kPer
+// keys (wave_rank), the block combines the four waves per digit, stages the
+// block's pairs locally sorted in LDS and writes each digit's run
+// contiguously.  A thread owns kPerT consecutive digits in the block-wide
+// digit scans.
 template <int kMaxBits, int kPer>
 __global__ void __launch_bounds__(kThreads) k_rs_scatter(const uint32_t* __restrict__ kin,
                                                          const uint32_t* __restrict__ vin, uint32_t* kout,
@@ -266,24 +353,8 @@ __global__ void __launch_bounds__(kThreads) k_rs_scatter(const uint32_t* __restr
   const int radix = 1 << bits;
   const uint32_t mask = static_cast<uint32_t>(radix - 1);
   const uint64_t lt = (1ull << lane) - 1ull;
-  // digit_base[j]: first global slot of digit tid * kPerT + j
-  uint32_t digit_base[kPerT];
-  {
-    uint32_t t[kPerT], sum = 0;
-#pragma unroll
-    for (int j = 0; j < kPerT; ++j) {
-      const int d = tid * kPerT + j;
-      t[j] = d < radix ? rowtot[d] : 0u;
-      sum += t[j];
-    }
-    uint32_t tot;
-    uint32_t run = block_excl_scan<uint32_t>(sum, lds, tot);
-#pragma unroll
-    for (int j = 0; j < kPerT; ++j) {
-      digit_base[j] = run;
-      run += t[j];
-    }
-  }
+  uint32_t digit_base[kPerT];  // first global slot of the thread's digits
+  digit_bases<kPerT>(rowtot, radix, lds, digit_base);
   for (int64_t lb = blockIdx.x; lb < nb; lb += gridDim.x) {
     for (int w = 0; w < kThreads / 64; ++w)
       for (int d = tid; d < radix; d += kThreads) s_cnt[w][d] = 0;
@@ -302,51 +373,12 @@ __global__ void __launch_bounds__(kThreads) k_rs_scatter(const uint32_t* __restr
       const bool valid = i < n;
       key[it] = valid ? kin[i] : 0u;
       val[it] = valid ? vin[i] : 0u;
-      const uint32_t dig = (key[it] >> shift) & mask;
-      uint64_t peers = __ballot(valid);
-      for (int b = 0; b < bits; ++b) {
-        const bool bit = (dig >> b) & 1u;
-        const uint64_t bal = __ballot(bit);
-        peers &= bit ? bal : ~bal;
-      }
-      uint32_t old = 0;
-      if (valid) old = s_cnt[wid][dig];
-      rank[it] = old + static_cast<uint32_t>(__popcll(peers & lt));
-      __builtin_amdgcn_wave_barrier();
-      if (valid && (peers & lt) == 0) s_cnt[wid][dig] = old + static_cast<uint32_t>(__popcll(peers));
-      __builtin_amdgcn_wave_barrier();
-      if (!valid) rank[it] = 0xffffffffu;
+      rank[it] = wave_rank((key[it] >> shift) & mask, valid, bits, s_cnt[wid], lt);
     }
     __syncthreads();
     // phase 2: per digit, combine the waves and scan over digits
-    {
-      uint32_t c[kPerT][kThreads / 64], tot[kPerT], sum = 0;
-#pragma unroll
-      for (int j = 0; j < kPerT; ++j) {
-        const int d = tid * kPerT + j;
-        tot[j] = 0;
-        for (int w = 0; w < kThreads / 64; ++w) {
-          c[j][w] = d < radix ? s_cnt[w][d] : 0u;
-          tot[j] += c[j][w];
-        }
-        sum += tot[j];
-      }
-      uint32_t all;
-      uint32_t off = block_excl_scan<uint32_t>(sum, lds, all);
-#pragma unroll
-      for (int j = 0; j < kPerT; ++j) {
-        const int d = tid * kPerT + j;
-        if (d < radix) {
-          s_off[d] = off;
-          uint32_t run = off;
-          for (int w = 0; w < kThreads / 64; ++w) {
-            s_cnt[w][d] = run;
-            run += c[j][w];
-          }
-        }
-        off += tot[j];
-      }
-    }
+    uint32_t tot[kPerT];
+    combine_digits<kR, kPerT>(s_cnt, s_off, radix, lds, tot);
     __syncthreads();
     // phase 3: stage locally sorted
 #pragma unroll
@@ -544,15 +576,18 @@ __global__ void __launch_bounds__(kThreads) k_row_count(ViewSet vs, const uint32
   if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
 
-// Index of each visible Gaussian's first rectangle row (row_off[k]) and, for
-// the adjoint, row_base[g] = row_off[k] - y0 (mod 2^32).
+constexpr int kRowSort = 1024;  // rectangle rows per block of the tile-row pass
+
+// Index of each visible Gaussian's first rectangle row (row_off[k]), for the
+// adjoint row_base[g] = row_off[k] - y0 (mod 2^32), and, for the tile-row
+// pass, the owner starts[b] of row kRowSort b.
 __global__ void __launch_bounds__(kThreads) k_row_base(ViewSet vs, const uint32_t* __restrict__ order,
                                                        const float* __restrict__ xy,
                                                        const int32_t* __restrict__ radius, const uint32_t* n_dev,
                                                        int64_t n_host,
                                                        const unsigned long long* __restrict__ row_partials,
                                                        const uint32_t* __restrict__ counters, uint32_t* row_off,
-                                                       uint32_t* row_base) {
+                                                       uint32_t* row_base, uint32_t* starts) {
   __shared__ unsigned long long lds[5];
   if (counters[2]) return;
   const int64_t n = live_count(n_dev, n_host);
@@ -571,6 +606,11 @@ __global__ void __launch_bounds__(kThreads) k_row_base(ViewSet vs, const uint32_
       row_partials[blockIdx.x];
   if (k < n) {
     row_off[k] = static_cast<uint32_t>(r0);
+    if (starts) {
+      const uint32_t b = static_cast<uint32_t>((r0 + kRowSort - 1) / kRowSort);
+      const uint64_t end = r0 + static_cast<uint32_t>(rect[3] - rect[1]);
+      for (uint64_t q = b; q * kRowSort < end; ++q) starts[q] = static_cast<uint32_t>(k);
+    }
     if (row_base) row_base[g] = static_cast<uint32_t>(r0) - static_cast<uint32_t>(rect[1]);
   }
 }
@@ -738,6 +778,562 @@ __global__ void __launch_bounds__(kThreads) k_row_emit(const uint4* __restrict__
   }
 }
 
+// ------------------------------------------------------------------ step 4 by tile rows (culled lists)
+// A rectangle row's instances are consecutive tiles of one tile row, so the
+// culled lists need no sort of instances by tile id, which moved every
+// instance's 8 bytes seven times: the row records (an eighth of the instances
+// on large views) are sorted by tile row, which is one radix pass that also
+// leaves the empty ones behind, and then every tile row's records, still in
+// depth order, are expanded and dealt to their columns in one pass that
+// writes the finished lists.  A record is a key (tile row << 16 | last
+// reached column << 8 | first) and its Gaussian; a row with nothing reached
+// has last column 255.
+constexpr int kRowChunk = 256;   // sorted records per block iteration of the expansion, all of one tile row
+constexpr int kMaxCols = 255;    // widest tile grid of the packed keys
+constexpr int kRun = 4096;       // instances expanded at a time
+
+__device__ __forceinline__ uint32_t key_first(uint32_t k) { return k & 255u; }
+__device__ __forceinline__ uint32_t key_len(uint32_t k) {  // 255: nothing reached
+  const uint32_t c1 = (k >> 8) & 255u;
+  return c1 == 255u ? 0u : c1 + 1u - (k & 255u);
+}
+
+// First global tile id and number of columns of global tile row y (0 columns
+// past the last live row).
+__device__ __forceinline__ int2 tile_row_of(const ViewSet& vs, int y) {
+  if (!vs.table) return make_int2(y * vs.one.GX, y < vs.one.GY ? vs.one.GX : 0);
+  int lo = 0, hi = live_views(vs) - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (vs.table[mid].row_off <= y) lo = mid; else hi = mid - 1;
+  }
+  const View& v = vs.table[lo];
+  const int ty = y - v.row_off;
+  return make_int2(static_cast<int>(v.tile_off) + ty * v.GX, ty < v.GY ? v.GX : 0);
+}
+
+// Of 64 marks, those of lanes 0 .. lane.
+__device__ __forceinline__ uint32_t marks_upto(uint32_t lo, uint32_t hi, int lane) {
+  const uint32_t own = (lane < 32 ? lo >> lane : hi >> (lane - 32)) & 1u;
+  return __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, own));
+}
+
+// One thread per rectangle row, kRowSort consecutive rows per block
+// iteration, with the owners staged as in k_row_intervals; a bit per row
+// marks where an owner starts, and a row's owner is the count of marks up to
+// it.  Writes each row's
+// record, the block's record counts per tile row (hist[y][block], y < nrows)
+// and the sum of its reached tiles per 256 rows.
+template <int kR>
+__global__ void __launch_bounds__(kRowSort) k_row_keys(ViewSet vs, const uint32_t* __restrict__ order,
+                                                       const float* __restrict__ xy,
+                                                       const float* __restrict__ conic_op,
+                                                       const int32_t* __restrict__ radius,
+                                                       const uint32_t* __restrict__ row_off,
+                                                       const uint32_t* __restrict__ starts,
+                                                       const uint32_t* __restrict__ num_rows,
+                                                       const uint32_t* __restrict__ counters, int nrows, int64_t cols,
+                                                       uint32_t* keys, uint32_t* vals, uint32_t* hist,
+                                                       unsigned long long* tile_partials) {
+  __shared__ uint32_t s_off[kRowSort];
+  __shared__ uint32_t s_g[kRowSort];
+  __shared__ int2 s_x[kRowSort];   // rectangle columns [x, y)
+  __shared__ int4 s_y[kRowSort];   // rectangle rows [x, y), the view's height and first global tile row
+  __shared__ ReachRows s_rr[kRowSort];
+  __shared__ uint32_t s_h[kR];
+  __shared__ uint32_t s_w[kRowSort / 64];
+  __shared__ uint32_t s_mark[kRowSort / 32];  // bit i: an owner's first row of the block is row i
+  __shared__ uint32_t s_mbase[kRowSort / 64]; // owners before each 64 rows
+  if (counters[2]) return;
+  const int64_t R = *num_rows;
+  const int64_t nvis = counters[1];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int64_t nblocks = (R + kRowSort - 1) / kRowSort;
+  for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
+    const int64_t i0 = blk * kRowSort;
+    const int64_t i1 = min(R, i0 + kRowSort);
+    for (int d = tid; d < nrows; d += kRowSort) s_h[d] = 0;
+    if (tid < kRowSort / 32) s_mark[tid] = 0;
+    __syncthreads();
+    // the block's owners: up to the next block's first, which may own rows of both
+    const int64_t k0 = starts[blk];
+    const int64_t k1 = blk + 1 < nblocks ? static_cast<int64_t>(starts[blk + 1]) : nvis - 1;
+    const int cnt = static_cast<int>(min<int64_t>(kRowSort, k1 - k0 + 1));
+    if (tid < cnt) {
+      const uint32_t g = order[k0 + tid];
+      float2 m;
+      int32_t rect[4];
+      const View& v = rect_of(vs, xy, radius, g, m, rect);
+      const float4 co = reinterpret_cast<const float4*>(conic_op)[g];
+      const uint32_t off = row_off[k0 + tid];
+      const uint32_t at = tid == 0 ? 0u : off - static_cast<uint32_t>(i0);
+      if (at < kRowSort) atomicOr(&s_mark[at >> 5], 1u << (at & 31u));
+      s_off[tid] = off;
+      s_g[tid] = g;
+      s_x[tid] = make_int2(rect[0], rect[2]);
+      s_y[tid] = make_int4(rect[1], rect[3], v.H, v.row_off);
+      s_rr[tid] = reach_rows_init(m.x, m.y, co.x, co.y, co.z, co.w);
+    }
+    __syncthreads();
+    if (wid == 0) {
+      const uint32_t m = lane < kRowSort / 64 ? __popc(s_mark[2 * lane]) + __popc(s_mark[2 * lane + 1]) : 0u;
+      const uint32_t x = wave_incl_scan<uint32_t>(m, lane);
+      if (lane < kRowSort / 64) s_mbase[lane] = x - m;
+    }
+    __syncthreads();
+    const int64_t i = i0 + tid;
+    uint32_t len = 0;
+    if (i < i1) {
+      const uint32_t ui = static_cast<uint32_t>(i);
+      const uint32_t lo = s_mbase[wid] + marks_upto(s_mark[2 * wid], s_mark[2 * wid + 1], lane) - 1u;
+      const int4 ry = s_y[lo];
+      const int ty = ry.x + static_cast<int>(ui - s_off[lo]);
+      int c0 = 0, c1 = -1;
+      if (ty < ry.y) reach_row(s_rr[lo], ty, ry.z, s_x[lo].x, s_x[lo].y, c0, c1);
+      len = c1 >= c0 ? static_cast<uint32_t>(c1 - c0 + 1) : 0u;
+      const uint32_t y = static_cast<uint32_t>(ry.w + ty);
+      keys[i] = (y << 16) | (len ? static_cast<uint32_t>(c1) << 8 : 255u << 8) | static_cast<uint32_t>(c0);
+      vals[i] = s_g[lo];
+      if (len) atomicAdd(&s_h[y], 1u);
+    }
+    const uint32_t x = wave_incl_scan<uint32_t>(len, lane);
+    if (lane == 63) s_w[wid] = x;
+    __syncthreads();
+    if (tid < kRowSort / 256 && i0 + 256 * tid < i1)
+      tile_partials[blk * (kRowSort / 256) + tid] =
+          static_cast<unsigned long long>(s_w[4 * tid]) + s_w[4 * tid + 1] + s_w[4 * tid + 2] + s_w[4 * tid + 3];
+    for (int d = tid; d < nrows; d += kRowSort) hist[d * cols + blk] = s_h[d];
+    __syncthreads();
+  }
+}
+
+// Block 0: the exclusive scan of the tile sums and the capacity check of the
+// reached tiles; block 1 + y: the exclusive scan of tile row y's block counts.
+__global__ void __launch_bounds__(1024) k_row_scans(unsigned long long* partials, const uint32_t* num_rows,
+                                                    uint32_t* counters, int64_t cap, uint32_t* hist, int64_t cols,
+                                                    uint32_t* rowtot) {
+  __shared__ unsigned long long wsum[17];
+  const int64_t R = *num_rows;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  if (blockIdx.x == 0) {
+    if (counters[2]) return;
+    scan_partials_block(partials, (R + 255) / 256, wsum, counters, cap, counters + 2, counters + 3);
+    return;
+  }
+  uint32_t* row = hist + static_cast<int64_t>(blockIdx.x - 1) * cols;
+  const int64_t nb = (R + kRowSort - 1) / kRowSort;
+  uint32_t* w32 = reinterpret_cast<uint32_t*>(wsum);
+  uint32_t carry = 0;
+  for (int64_t base = 0; base < nb; base += 4096) {
+    const int64_t i0 = base + tid * 4;
+    uint32_t v[4], sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = i0 + k < nb ? row[i0 + k] : 0u;
+      sum += v[k];
+    }
+    const uint32_t x = wave_incl_scan<uint32_t>(sum, lane);
+    if (lane == 63) w32[wid] = x;
+    __syncthreads();
+    uint32_t run = carry + x - sum, all = 0;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wid) run += w32[w];
+      all += w32[w];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (i0 + k < nb) row[i0 + k] = run;
+      run += v[k];
+    }
+    carry += all;
+    __syncthreads();
+  }
+  if (tid == 0) rowtot[blockIdx.x - 1] = carry;
+}
+
+// The tile-row pass: k_rs_scatter over the records' tile rows, leaving out
+// the empty ones.  A wave's 256 records are also one block of the tile sums,
+// so it knows every record's first instance and writes the adjoint's row
+// records brows[i] = (offset, first column | count << 16) and, for a
+// Gaussian's first row, first[g].
+template <int kR>
+__global__ void __launch_bounds__(kThreads) k_row_scatter(const uint32_t* __restrict__ kin,
+                                                          const uint32_t* __restrict__ vin, uint32_t* kout,
+                                                          uint32_t* vout, const uint32_t* __restrict__ num_rows,
+                                                          const uint32_t* __restrict__ counters, int bits,
+                                                          const uint32_t* __restrict__ hist, int64_t cols, int nrows,
+                                                          const uint32_t* __restrict__ rowtot,
+                                                          const unsigned long long* __restrict__ tile_partials,
+                                                          uint2* brows, uint32_t* first) {
+  constexpr int kPer = kRowSort / kThreads;
+  constexpr int kPerT = kR / kThreads;
+  __shared__ uint32_t s_cnt[kThreads / 64][kR];
+  __shared__ uint32_t s_off[kR];
+  __shared__ uint32_t s_gbase[kR];
+  __shared__ uint32_t s_k[kRowSort];
+  __shared__ uint32_t s_v[kRowSort];
+  __shared__ uint32_t lds[5];
+  if (counters[2]) return;
+  const int64_t n = *num_rows;
+  const int64_t nb = (n + kRowSort - 1) / kRowSort;
+  if (static_cast<int64_t>(blockIdx.x) >= nb) return;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint64_t lt = (1ull << lane) - 1ull;
+  uint32_t digit_base[kPerT];
+  digit_bases<kPerT>(rowtot, nrows, lds, digit_base);
+  for (int64_t lb = blockIdx.x; lb < nb; lb += gridDim.x) {
+    for (int w = 0; w < kThreads / 64; ++w)
+      for (int d = tid; d < nrows; d += kThreads) s_cnt[w][d] = 0;
+#pragma unroll
+    for (int j = 0; j < kPerT; ++j) {
+      const int d = tid * kPerT + j;
+      if (d < nrows) s_gbase[d] = digit_base[j] + hist[d * cols + lb];
+    }
+    __syncthreads();
+    const int64_t wbase = lb * kRowSort + static_cast<int64_t>(wid) * 256;
+    uint32_t inst = wbase < n ? static_cast<uint32_t>(tile_partials[lb * (kRowSort / 256) + wid]) : 0u;
+    uint32_t key[kPer], val[kPer], rank[kPer];
+#pragma unroll
+    for (int it = 0; it < kPer; ++it) {
+      const int64_t i = wbase + it * 64 + lane;
+      const bool in = i < n;
+      key[it] = in ? kin[i] : 255u << 8;
+      val[it] = in ? vin[i] : 0u;
+      const uint32_t len = key_len(key[it]);
+      const uint32_t x = wave_incl_scan<uint32_t>(len, lane);
+      const uint32_t e = inst + x - len;
+      inst += __shfl(x, 63, 64);
+      uint32_t before = __shfl_up(val[it], 1, 64);  // the record before belongs to the same Gaussian, or this is its first
+      if (lane == 0) before = in && i > 0 ? vin[i - 1] : ~val[it];
+      if (in && brows) brows[i] = make_uint2(e, key_first(key[it]) | (len << 16));
+      if (in && first && before != val[it]) first[val[it]] = e;
+      rank[it] = wave_rank(key[it] >> 16, len > 0, bits, s_cnt[wid], lt);
+    }
+    __syncthreads();
+    uint32_t tot[kPerT];
+    combine_digits<kR, kPerT>(s_cnt, s_off, nrows, lds, tot);
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kPer; ++it) {
+      if (rank[it] != 0xffffffffu) {
+        const uint32_t p = s_cnt[wid][key[it] >> 16] + rank[it];
+        s_k[p] = key[it];
+        s_v[p] = val[it];
+      }
+    }
+    __syncthreads();
+    // the records of all digits (lds[4]: the block scan's total)
+    const int live = static_cast<int>(lds[4]);
+    for (int p = tid; p < live; p += kThreads) {
+      const uint32_t k = s_k[p];
+      const uint32_t o = s_gbase[k >> 16] + (static_cast<uint32_t>(p) - s_off[k >> 16]);
+      kout[o] = k;
+      vout[o] = s_v[p];
+    }
+    __syncthreads();
+  }
+}
+
+// First sorted record and first chunk of every tile row (index nrows: the
+// totals), from the rows' record counts.
+template <int kR>
+__device__ __forceinline__ void row_tables(const uint32_t* __restrict__ rowtot, int nrows, uint32_t* s_rec,
+                                           uint32_t* s_chunk, uint32_t* lds) {
+  constexpr int kPerT = kR / kThreads;
+  uint32_t t[kPerT], rec = 0, chunk = 0, all_rec, all_chunk;
+#pragma unroll
+  for (int j = 0; j < kPerT; ++j) {
+    const int d = threadIdx.x * kPerT + j;
+    t[j] = d < nrows ? rowtot[d] : 0u;
+    rec += t[j];
+    chunk += (t[j] + kRowChunk - 1) / kRowChunk;
+  }
+  uint32_t r = block_excl_scan<uint32_t>(rec, lds, all_rec);
+  uint32_t c = block_excl_scan<uint32_t>(chunk, lds, all_chunk);
+#pragma unroll
+  for (int j = 0; j < kPerT; ++j) {
+    const int d = threadIdx.x * kPerT + j;
+    if (d < nrows) { s_rec[d] = r; s_chunk[d] = c; }
+    r += t[j];
+    c += (t[j] + kRowChunk - 1) / kRowChunk;
+  }
+  if (threadIdx.x == 0) { s_rec[nrows] = all_rec; s_chunk[nrows] = all_chunk; }
+  __syncthreads();
+}
+
+// Instances per column of each chunk: every record adds 1 at its first
+// column and takes it away behind its last, and the prefix sum counts them.
+// chunks[c] = (first record, last + 1, first tile id of its row, instances);
+// *num_chunks counts them.
+template <int kR>
+__global__ void __launch_bounds__(kThreads) k_col_hist(ViewSet vs, const uint32_t* __restrict__ keys,
+                                                       const uint32_t* __restrict__ rowtot,
+                                                       const uint32_t* __restrict__ counters, int nrows, int ld,
+                                                       uint32_t* chist, uint32_t* chunks, uint32_t* num_chunks) {
+  __shared__ uint32_t s_rec[kR + 1], s_chunk[kR + 1];
+  __shared__ uint32_t s_d[kThreads];
+  __shared__ uint32_t s_sum[kThreads / 64];
+  __shared__ uint32_t lds[kThreads / 64 + 1];
+  if (counters[2]) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  row_tables<kR>(rowtot, nrows, s_rec, s_chunk, lds);
+  const uint32_t nchunks = s_chunk[nrows];
+  if (blockIdx.x == 0 && tid == 0) *num_chunks = nchunks;
+  for (uint32_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
+    int lo = 0, hi = nrows - 1;  // the tile row whose chunks include c
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (s_chunk[mid] <= c) lo = mid; else hi = mid - 1;
+    }
+    const uint32_t i0 = s_rec[lo] + (c - s_chunk[lo]) * kRowChunk;
+    const uint32_t i1 = min(s_rec[lo + 1], i0 + kRowChunk);
+    s_d[tid] = 0;
+    __syncthreads();
+    uint32_t sum = 0;
+    if (i0 + tid < i1) {
+      const uint32_t k = keys[i0 + tid];
+      const uint32_t len = key_len(k);
+      atomicAdd(&s_d[key_first(k)], 1u);
+      atomicSub(&s_d[key_first(k) + len], 1u);  // at most column 255
+      sum = len;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if (lane == 0) s_sum[tid >> 6] = sum;
+    __syncthreads();
+    const uint32_t v = s_d[tid];
+    sum = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+    uint32_t tot;
+    const uint32_t x = block_excl_scan<uint32_t>(v, lds, tot) + v;
+    if (tid < ld) chist[static_cast<int64_t>(c) * ld + tid] = x;
+    if (tid == 0) {
+      uint32_t* q = chunks + 4 * static_cast<int64_t>(c);
+      q[0] = i0;
+      q[1] = i1;
+      q[2] = static_cast<uint32_t>(tile_row_of(vs, lo).x);
+      q[3] = sum;
+    }
+  }
+}
+
+// Block y: the chunks' column counts of tile row y become each chunk's first
+// output slot of each column (tile rows in order, in one the columns in order,
+// in a column the chunks in order), and the row's tile ranges (empty: 0, 0)
+// are written.  256 threads a column range, or 128 where the grid is that
+// narrow, in as many segments of the chunks as fit.
+__global__ void __launch_bounds__(1024) k_col_scan(ViewSet vs, const uint32_t* __restrict__ rowtot,
+                                                   const uint32_t* __restrict__ counters, int ld, uint32_t* chist,
+                                                   const uint32_t* __restrict__ chunks, uint32_t* ranges) {
+  __shared__ uint32_t s_part[1024];
+  __shared__ uint32_t s_start[257];
+  __shared__ uint32_t s_w[16];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int y = blockIdx.x;
+  const int2 tr = tile_row_of(vs, y);
+  if (counters[2]) {  // over capacity: every list empty
+    if (tid < tr.y) ranges[2 * (tr.x + tid)] = ranges[2 * (tr.x + tid) + 1] = 0u;
+    return;
+  }
+  auto block_sum = [&](uint32_t v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (lane == 0) s_w[wid] = v;
+    __syncthreads();
+    uint32_t all = 0;
+    for (int w = 0; w < 16; ++w) all += s_w[w];
+    __syncthreads();
+    return all;
+  };
+  uint32_t v = 0;
+  for (int d = tid; d < y; d += 1024) v += (rowtot[d] + kRowChunk - 1) / kRowChunk;
+  const uint32_t c0 = block_sum(v);  // chunks of the rows before
+  v = 0;
+#pragma unroll 4
+  for (uint32_t c = tid; c < c0; c += 1024) v += chunks[4 * static_cast<int64_t>(c) + 3];
+  const uint32_t inst = block_sum(v);  // and their instances
+  const uint32_t nch = (rowtot[y] + kRowChunk - 1) / kRowChunk;
+  const int width = ld <= 128 ? 128 : 256;
+  const int col = tid & (width - 1), seg = tid / width, segs = 1024 / width;
+  const uint32_t q0 = static_cast<uint32_t>(static_cast<uint64_t>(nch) * seg / segs);
+  const uint32_t q1 = static_cast<uint32_t>(static_cast<uint64_t>(nch) * (seg + 1) / segs);
+  uint32_t* h = chist + static_cast<int64_t>(c0) * ld + col;
+  uint32_t sum = 0;
+  if (col < ld) {
+#pragma unroll 8
+    for (uint32_t q = q0; q < q1; ++q) sum += h[static_cast<int64_t>(q) * ld];
+  }
+  s_part[tid] = sum;
+  __syncthreads();
+  uint32_t run = 0, tot = 0;  // the segments before, and the column's total
+  for (int k = 0; k < segs; ++k) {
+    const uint32_t p = s_part[k * width + col];
+    if (k < seg) run += p;
+    tot += p;
+  }
+  // exclusive scan of the columns' totals (the first segment's threads)
+  const uint32_t x = wave_incl_scan<uint32_t>(tot, lane);
+  if (seg == 0 && lane == 63) s_w[wid] = x;
+  __syncthreads();
+  if (seg == 0) {
+    uint32_t b = inst + x - tot;
+    for (int w = 0; w < wid; ++w) b += s_w[w];
+    s_start[col] = b;
+    if (col < tr.y) {
+      ranges[2 * (tr.x + col)] = tot ? b : 0u;
+      ranges[2 * (tr.x + col) + 1] = tot ? b + tot : 0u;
+    }
+  }
+  __syncthreads();
+  run += s_start[col];
+  if (col < ld) {
+    uint32_t q = q0;
+    for (; q + 8 <= q1; q += 8) {
+      uint32_t t[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) t[k] = h[static_cast<int64_t>(q + k) * ld];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        h[static_cast<int64_t>(q + k) * ld] = run;
+        run += t[k];
+      }
+    }
+    for (; q < q1; ++q) {
+      const uint32_t t = h[static_cast<int64_t>(q) * ld];
+      h[static_cast<int64_t>(q) * ld] = run;
+      run += t;
+    }
+  }
+}
+
+// The expansion: a chunk's records become instances kRun at a time.  A bit
+// per instance marks where a record starts, so an instance's record is the
+// count of marks up to it.  Every instance then sets its record's bit in its
+// column's mask (256 records: eight words), which makes its rank in the
+// column the number of bits below; ranked, the instances are staged sorted in
+// LDS and written in runs at the chunk's first slots of its columns.
+//
+// Bound: the instances' 8 bytes out, 320 MB in 106 us on a 6M view; on a 1M
+// view (60 MB in 40 us) the latency of a chunk's eight steps, as 1,400 chunks
+// are one round of the chip: 512 threads 40 us, 256 44, 1,024 67.  Ranks by
+// wave_rank, a ballot per bit of the column: 75 us against 49 (256 threads).
+// Chunks of 128 records: 51 against 49, on the 6M view 145 against 120.
+constexpr int kExpand = 512;  // threads of the expansion
+__global__ void __launch_bounds__(kExpand) k_row_expand(const uint32_t* __restrict__ keys_in,
+                                                        const uint32_t* __restrict__ vals_in,
+                                                        const uint32_t* __restrict__ chist,
+                                                        const uint32_t* __restrict__ chunks,
+                                                        const uint32_t* __restrict__ num_chunks,
+                                                        const uint32_t* __restrict__ counters, int ld, uint32_t* keys,
+                                                        uint32_t* vals) {
+  constexpr int kPer = kRun / kExpand;
+  constexpr int kWords = kRowChunk / 32;
+  constexpr int kCols = kMaxCols + 1;
+  __shared__ uint32_t s_mask[kWords][kCols];  // per column: the records with an instance there
+  __shared__ uint16_t s_slot[kWords][kCols];  // staging slot of a column's first instance of each word
+  __shared__ uint32_t s_to[kCols];            // output slot minus staging slot of each column
+  __shared__ uint2 s_own[kRowChunk];          // Gaussian; first column minus first instance in the chunk
+  __shared__ uint32_t s_mark[kRun / 32];      // bit i: a record starts at instance i of the run
+  __shared__ uint32_t s_mbase[kRun / 64];     // records started before each 64 instances, in the chunk
+  __shared__ uint8_t s_t[kRun];
+  __shared__ uint32_t s_v[kRun];
+  __shared__ uint32_t lds[kExpand / 64 + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  if (counters[2]) return;
+  const uint32_t nchunks = *num_chunks;
+  for (uint32_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
+    const uint32_t* desc = chunks + 4 * static_cast<int64_t>(c);
+    const uint32_t i = desc[0] + tid, tile0 = desc[2], total = desc[3];
+    uint32_t key = 255u << 8, g = 0;
+    if (tid < kRowChunk && i < desc[1]) {
+      key = keys_in[i];
+      g = vals_in[i];
+    }
+    // the thread's column: its next output slot
+    uint32_t out = tid < ld ? chist[static_cast<int64_t>(c) * ld + tid] : 0u;
+    const uint32_t len = key_len(key);
+    uint32_t all;
+    const uint32_t pre = block_excl_scan<uint32_t, kExpand>(len, lds, all);
+    if (tid < kRowChunk) s_own[tid] = make_uint2(g, key_first(key) - pre);
+    uint32_t started = 0;  // records that start before the run
+    for (uint32_t r0 = 0; r0 < total; r0 += kRun) {
+      const uint32_t n = min(static_cast<uint32_t>(kRun), total - r0);
+      if (tid < kRun / 32) s_mark[tid] = 0;
+      for (int q = tid; q < kWords * kCols; q += kExpand) (&s_mask[0][0])[q] = 0;
+      __syncthreads();
+      if (len > 0 && pre >= r0 && pre < r0 + n) atomicOr(&s_mark[(pre - r0) >> 5], 1u << ((pre - r0) & 31u));
+      __syncthreads();
+      if (wid == 0) {
+        const uint32_t m = static_cast<uint32_t>(__popc(s_mark[2 * lane]) + __popc(s_mark[2 * lane + 1]));
+        const uint32_t x = wave_incl_scan<uint32_t>(m, lane);
+        s_mbase[lane] = started + x - m;
+        if (lane == 63) lds[0] = started + x;
+      }
+      __syncthreads();
+      started = lds[0];
+      // whole 64s per wave, as even as they go
+      const uint32_t per = ((n + 63) / 64 + kExpand / 64 - 1) / (kExpand / 64);
+      uint32_t at[kPer], val[kPer];  // record in the chunk << 8 | column; Gaussian
+#pragma unroll
+      for (int it = 0; it < kPer; ++it) {
+        const uint32_t grp = wid * per + it;
+        const uint32_t q = grp * 64 + lane;
+        at[it] = 0;
+        val[it] = 0;
+        if (static_cast<uint32_t>(it) < per && q < n) {
+          const uint32_t rec = s_mbase[grp] + marks_upto(s_mark[2 * grp], s_mark[2 * grp + 1], lane) - 1u;
+          const uint2 o = s_own[rec];
+          const uint32_t x = o.y + r0 + q;
+          atomicOr(&s_mask[rec >> 5][x], 1u << (rec & 31u));
+          at[it] = rec << 8 | x;
+          val[it] = o.x;
+        }
+      }
+      __syncthreads();
+      {
+        uint32_t m[kWords], cnt = 0;
+        if (tid < kCols) {
+#pragma unroll
+          for (int w = 0; w < kWords; ++w) {
+            m[w] = __popc(s_mask[w][tid]);
+            cnt += m[w];
+          }
+        }
+        uint32_t slot = block_excl_scan<uint32_t, kExpand>(cnt, lds, all);
+        if (tid < kCols) {
+          s_to[tid] = out - slot;
+          out += cnt;
+#pragma unroll
+          for (int w = 0; w < kWords; ++w) {
+            s_slot[w][tid] = static_cast<uint16_t>(slot);
+            slot += m[w];
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int it = 0; it < kPer; ++it) {
+        const uint32_t q = (wid * per + it) * 64 + lane;
+        if (static_cast<uint32_t>(it) < per && q < n) {
+          const uint32_t x = at[it] & 255u, rec = at[it] >> 8;
+          const uint32_t below = s_mask[rec >> 5][x] & ((1u << (rec & 31u)) - 1u);
+          const uint32_t p = s_slot[rec >> 5][x] + static_cast<uint32_t>(__popc(below));
+          s_t[p] = static_cast<uint8_t>(x);
+          s_v[p] = val[it];
+        }
+      }
+      __syncthreads();
+      for (uint32_t p = tid; p < n; p += kExpand) {
+        const uint32_t t = s_t[p];
+        const uint32_t o = s_to[t] + p;
+        keys[o] = tile0 + t;
+        vals[o] = s_v[p];
+      }
+      __syncthreads();
+    }
+    __syncthreads();
+  }
+}
+
 // Four keys a thread (one 16-byte read, plus the keys either side): the
 // tile of each is a range's first entry where the key before differs, its
 // last where the key after does.
@@ -822,6 +1418,73 @@ static hipError_t radix_pass(const uint32_t* kin, const uint32_t* vin, uint32_t*
   return hipGetLastError();
 }
 
+// Device arrays of the tile-row path: the records before their sort lie in the
+// unused halves of keys and vals, everything else in the rows scratch.
+struct RowSort {
+  int nrows, ld, row_bits;
+  int64_t cols;  // blocks of the tile-row pass at full capacity
+  uint32_t *rkeys, *rvals, *skeys, *svals, *hist, *chist, *rowtot, *starts, *chunks, *num_chunks;
+};
+
+// The tile-row path takes every culled launch whose view widths fit the packed
+// keys, whose tile rows fit one digit (10 bits) and whose tables fit the rows
+// scratch, which is sized for the other path (from a capacity of some 100
+// instances a tile row of 120 columns on they do).  It was the faster one at
+// every size measured, from 2,000 Gaussians at 128x96 to 6M.
+static bool plan_rows(const ViewSet& vs, const pvg_bins* bins, uint32_t* scratch, RowSort& r) {
+  const int64_t cap = bins->capacity;
+  if (!bins->tile_cull || vs.total_rows < 1 || vs.total_rows > 1024 || vs.max_cols > kMaxCols) return false;
+  r.nrows = static_cast<int>(vs.total_rows);
+  r.ld = vs.max_cols;
+  r.cols = cdiv(cap, kRowSort);
+  const int64_t hist = r.nrows * r.cols, chunks = cdiv(cap, kRowChunk) + r.nrows;
+  if (hist + chunks * (r.ld + 4) + r.nrows + r.cols + 1 > 2 * cap) return false;
+  r.row_bits = 0;
+  while ((1 << r.row_bits) < r.nrows) ++r.row_bits;
+  r.rkeys = bins->keys + cap;
+  r.rvals = bins->vals + cap;
+  r.skeys = scratch;
+  r.svals = r.skeys + cap;
+  r.hist = r.svals + cap;
+  r.chist = r.hist + hist;
+  r.chunks = r.chist + chunks * r.ld;
+  r.rowtot = r.chunks + 4 * chunks;
+  r.starts = r.rowtot + r.nrows;
+  r.num_chunks = r.starts + r.cols;
+  return true;
+}
+
+constexpr int64_t kRowGrid = 2048;  // physical blocks of the tile-row kernels (two to four rounds of the chip)
+
+template <int kR>
+static void launch_row_keys(const ViewSet& vs, const RowSort& r, const uint32_t* order, const Geom& geom,
+                            const uint32_t* row_off, const uint32_t* num_rows, pvg_bins* bins,
+                            unsigned long long* partials, hipStream_t s) {
+  // two blocks a CU, all that its LDS holds; 2,048 blocks, most of them empty: 26 us for 23
+  const unsigned nb = static_cast<unsigned>(std::min<int64_t>(512, std::max<int64_t>(1, r.cols)));
+  hipLaunchKernelGGL(k_row_keys<kR>, dim3(nb), dim3(kRowSort), 0, s, vs, order, geom.xy, geom.conic_op, geom.radius,
+                     row_off, r.starts, num_rows, bins->counters, r.nrows, r.cols, r.rkeys, r.rvals, r.hist, partials);
+  hipLaunchKernelGGL(k_row_scans, dim3(static_cast<unsigned>(1 + r.nrows)), dim3(1024), 0, s, partials, num_rows,
+                     bins->counters, bins->capacity, r.hist, r.cols, r.rowtot);
+}
+
+// max_rows bounds the rectangle rows (the capacity, or the counted rows).
+template <int kR>
+static void launch_row_lists(const ViewSet& vs, const RowSort& r, int64_t max_rows, const uint32_t* num_rows,
+                             pvg_bins* bins, const unsigned long long* partials, hipStream_t s) {
+  const unsigned nb = static_cast<unsigned>(std::min(kRowGrid, std::max<int64_t>(1, cdiv(max_rows, kRowSort))));
+  hipLaunchKernelGGL(k_row_scatter<kR>, dim3(nb), dim3(kThreads), 0, s, r.rkeys, r.rvals, r.skeys, r.svals, num_rows,
+                     bins->counters, r.row_bits, r.hist, r.cols, r.nrows, r.rowtot, partials,
+                     reinterpret_cast<uint2*>(bins->rows), bins->first);
+  const unsigned nc = static_cast<unsigned>(std::min(2 * kRowGrid, cdiv(max_rows, kRowChunk) + r.nrows));
+  hipLaunchKernelGGL(k_col_hist<kR>, dim3(nc), dim3(kThreads), 0, s, vs, r.skeys, r.rowtot, bins->counters, r.nrows,
+                     r.ld, r.chist, r.chunks, r.num_chunks);
+  hipLaunchKernelGGL(k_col_scan, dim3(static_cast<unsigned>(r.nrows)), dim3(1024), 0, s, vs, r.rowtot, bins->counters,
+                     r.ld, r.chist, r.chunks, bins->ranges);
+  hipLaunchKernelGGL(k_row_expand, dim3(nc), dim3(kExpand), 0, s, r.skeys, r.svals, r.chist, r.chunks, r.num_chunks,
+                     bins->counters, r.ld, bins->keys, bins->vals);
+}
+
 int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp, const BinPlan& plan,
                  int sync_count, hipStream_t s) {
   char* base = static_cast<char*>(tmp);
@@ -867,6 +1530,8 @@ int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp,
   unsigned long long* partials2 = reinterpret_cast<unsigned long long*>(base + plan.off_partials2);
   uint4* rows = reinterpret_cast<uint4*>(base + plan.off_rows);
   uint32_t* num_rows = reinterpret_cast<uint32_t*>(base + plan.off_num_rows);
+  RowSort rs{};
+  const bool by_rows = plan_rows(vs, bins, reinterpret_cast<uint32_t*>(rows), rs);
   const unsigned nbv_max = static_cast<unsigned>(std::max<int64_t>(1, cdiv(n, kScanBlock)));
   // instance counts in depth order and the capacity check: rectangle tiles, or
   // (culled) rectangle rows, their reached intervals and the reached tiles
@@ -888,12 +1553,17 @@ int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp,
                          static_cast<const int64_t*>(nullptr), n, kRowBlock, num_rows, cap, counters + 2,
                          counters + 3, static_cast<const uint32_t*>(nullptr));
       hipLaunchKernelGGL(k_row_base, dim3(nbr), dim3(kThreads), 0, s, vs, order, geom.xy, geom.radius, counters + 1,
-                         n, partials, counters, offsets, bins->row_base);
-      hipLaunchKernelGGL(k_row_intervals, dim3(nrb), dim3(kThreads), 0, s, vs, order, geom.xy, geom.conic_op,
-                         geom.radius, offsets, num_rows, counters, rows, partials2);
-      hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partials2, num_rows,
-                         static_cast<const int64_t*>(nullptr), int64_t{0}, kRowBlock, counters, cap, counters + 2,
-                         counters + 3, counters + 2);
+                         n, partials, counters, offsets, bins->row_base, by_rows ? rs.starts : nullptr);
+      if (by_rows) {
+        (rs.nrows <= 256 ? launch_row_keys<256> : launch_row_keys<1024>)(vs, rs, order, geom, offsets, num_rows, bins,
+                                                                         partials2, s);
+      } else {
+        hipLaunchKernelGGL(k_row_intervals, dim3(nrb), dim3(kThreads), 0, s, vs, order, geom.xy, geom.conic_op,
+                           geom.radius, offsets, num_rows, counters, rows, partials2);
+        hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partials2, num_rows,
+                           static_cast<const int64_t*>(nullptr), int64_t{0}, kRowBlock, counters, cap, counters + 2,
+                           counters + 3, counters + 2);
+      }
     }
     PVG_HIP(hipGetLastError());
   }
@@ -916,6 +1586,12 @@ int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp,
     m_grid = host_counts[0];
     vis_grid = host_counts[1];
     row_grid = host_rows;
+  }
+  if (by_rows && n > 0 && vis_grid > 0 && row_grid > 0) {
+    StageScope sc(PVG_STAGE_TILE_SORT, s);
+    (rs.nrows <= 256 ? launch_row_lists<256> : launch_row_lists<1024>)(vs, rs, row_grid, num_rows, bins, partials2, s);
+    PVG_HIP(hipGetLastError());
+    return PVG_OK;
   }
   const int passes = plan.tile_passes;
   const int start = passes & 1;  // so that the last pass lands in buffer 0

@@ -41,6 +41,7 @@ struct View {
   float bg[3];
   int64_t geom_off;  // first slot of this view's Gaussians in the batch's geom arrays
   int64_t tile_off;  // first global tile id of this view
+  int32_t row_off;   // first global tile row of this view
   float* img;        // [3][H][W]
   float* final_T;    // [H][W]
   int32_t* n_contrib;// [H][W]
@@ -80,6 +81,8 @@ struct ViewSet {
   int32_t nviews;       // views (single: 1; batched: table capacity)
   int64_t total_gauss;  // sum of the views' n (batched: grid bound)
   int64_t total_tiles;  // sum of the views' GX * GY (batched: grid bound)
+  int64_t total_rows;   // sum of the views' GY (batched: bound; 0: not known)
+  int32_t max_cols;     // the widest view's GX (batched: bound)
 };
 
 #ifdef __HIPCC__

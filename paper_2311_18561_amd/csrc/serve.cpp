@@ -10,6 +10,7 @@
 // captured once per (Gaussian, tile) grid bucket and replayed as a hipGraph
 // whose first node copies the batch's view table from pinned host memory.
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <condition_variable>
 #include <cstring>
@@ -80,7 +81,7 @@ struct Lane {
   View* d_views = nullptr;
   void* h_stage = nullptr;      // pinned: Header + views
   uint32_t* h_counters = nullptr;  // pinned: copy of bins.counters after the batch
-  std::map<std::pair<int64_t, int64_t>, hipGraphExec_t> graphs;
+  std::map<std::array<int64_t, 4>, hipGraphExec_t> graphs;  // by the grid bounds: Gaussians, tiles, tile rows, columns
   std::vector<Ticket*> batch;
   bool busy = false;
   int64_t t_launch = 0;
@@ -195,7 +196,8 @@ int launch_batch(pvg_server* s, Lane& L) {
   if (stub(s)) return PVG_OK;
   Header* h = static_cast<Header*>(L.h_stage);
   View* views = reinterpret_cast<View*>(static_cast<char*>(L.h_stage) + sizeof(Header));
-  int64_t og = 0, ot = 0, op = 0;
+  int64_t og = 0, ot = 0, op = 0, orow = 0;
+  int32_t cols = 1;
   for (size_t k = 0; k < L.batch.size(); ++k) {
     const Ticket* t = L.batch[k];
     pvg_frame fr{};
@@ -204,6 +206,7 @@ int launch_batch(pvg_server* s, Lane& L) {
     View v = make_view(&t->g, &t->req.camera, &fr);
     v.geom_off = og;
     v.tile_off = ot;
+    v.row_off = static_cast<int32_t>(orow);
     v.img = t->req.dst;
     v.final_T = L.final_T + op;
     v.n_contrib = L.n_contrib + op;
@@ -211,6 +214,8 @@ int launch_batch(pvg_server* s, Lane& L) {
     og += t->n;
     ot += t->tiles;
     op += t->pixels;
+    orow += v.GY;
+    cols = std::max(cols, v.GX);
   }
   h->live[0] = og;
   h->live[1] = ot;
@@ -228,9 +233,13 @@ int launch_batch(pvg_server* s, Lane& L) {
   vs.nviews = s->cfg.max_batch;
   vs.total_gauss = gb;
   vs.total_tiles = tb;
+  if (orow <= 1024 && cols <= 255) {  // else 0: the lists are not built by tile rows
+    vs.total_rows = next_pow2(orow, 256);
+    vs.max_cols = cols <= 128 ? 128 : 255;
+  }
   const BinPlan plan = plan_bins(gb, tb, s->cfg.instance_capacity);
   if (!s->cfg.use_graphs) return enqueue_batch(s, L, vs, plan);
-  const auto key = std::make_pair(gb, tb);
+  const std::array<int64_t, 4> key{gb, tb, vs.total_rows, vs.max_cols};
   auto it = L.graphs.find(key);
   if (it == L.graphs.end()) {
     PVG_HIP(hipStreamBeginCapture(L.stream, hipStreamCaptureModeThreadLocal));
