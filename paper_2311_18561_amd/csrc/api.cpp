@@ -562,16 +562,17 @@ int pvg_render_bwd_views_channels(const pvg_gaussians* g, int32_t n_views, const
   BwdViews pk;
   std::memset(&pk, 0, sizeof(pk));
   bool first_group = true;
-  // Views go to g2d slots in turn.  The per-Gaussian pass runs per group of
-  // `group` views: concurrently, one view per side stream, so the pass over
-  // a finished group overlaps the next group's compositing adjoints; the
-  // side streams wait for the caller's stream only when slots are reused.
+  // Views go to g2d slots in turn.  One per-Gaussian pass takes all views of
+  // a render time up to the slots' number; it sums them by groups of one view
+  // per side stream.  The side streams wait for the caller's stream only when
+  // slots are reused.
   const int32_t group = serial ? kMaxBwdViews : regions;
   int32_t used_slots = 0;
   auto flush = [&]() -> int {
     if (pk.nv == 0) return PVG_OK;
     int st = join();
     if (st != PVG_OK) return st;
+    pk.group = group;
     PVG_HIP(launch_preprocess_bwd(pk, *grad, first_group ? accumulate : 1, s));
     first_group = false;
     pk.nv = 0;
@@ -632,7 +633,7 @@ int pvg_render_bwd_views_channels(const pvg_gaussians* g, int32_t n_views, const
     pk.g2d[pk.nv] = g2d;
     pk.feat_grad[pk.nv] = channels ? channels[k].feature_grad : nullptr;
     ++pk.nv;
-    if (pk.nv == group || used_slots == kMaxBwdViews) {
+    if (used_slots == kMaxBwdViews) {
       const int st = flush();
       if (st != PVG_OK) return st;
     }
@@ -715,6 +716,7 @@ int pvg_render_features_bwd(const pvg_gaussians* g, int32_t n_views, const pvg_c
   uint8_t* vis = reinterpret_cast<uint8_t*>(base + off_vis);
   BwdViews pk;
   std::memset(&pk, 0, sizeof(pk));
+  pk.group = kMaxBwdViews;
   bool first_group = true;
   auto flush = [&]() -> int {
     if (pk.nv == 0) return PVG_OK;

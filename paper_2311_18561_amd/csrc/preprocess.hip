@@ -342,58 +342,79 @@ __device__ __forceinline__ void adjoint_features(const GaussTime& G, const ViewS
   acc.l += vdot * e * (0.5f * beta / (l * l)) - S.drho * beta / (l * l);
 }
 
-// Adjoint of the per-Gaussian stage for up to kMaxBwdViews views of one set
-// of Gaussians at one render time (the host splits passes where t changes):
-// each Gaussian's gradient is summed over the views in registers (the SH part
-// in a second loop over the views, to bound register use) and written, or
-// added, once.  A Gaussian no view sees gets zeros (accumulate = 0) or is
-// left alone.
-// 3 waves per SIMD: the view loop fits in 168 registers without spilling
-__global__ void __launch_bounds__(256) k_preprocess_bwd(BwdViews pk, pvg_gaussians_grad grad,
-                                                                                             int accumulate) {
+// A thread's running sums in LDS (s[entry][thread]), so that they take no
+// registers through the view loop.
+__device__ __forceinline__ void acc_out(const GeoGrad& a, float (*s)[256]) {
+  const float* p = reinterpret_cast<const float*>(&a);
+#pragma unroll
+  for (int q = 0; q < static_cast<int>(sizeof(GeoGrad) / 4); ++q) s[q][threadIdx.x] = p[q];
+}
+__device__ __forceinline__ void acc_in(GeoGrad& a, float (*s)[256]) {
+  float* p = reinterpret_cast<float*>(&a);
+#pragma unroll
+  for (int q = 0; q < static_cast<int>(sizeof(GeoGrad) / 4); ++q) p[q] = s[q][threadIdx.x];
+}
+
+// dL/dsh of Gaussian i: written by every thread (zeros where no view sees it),
+// so that a wave's stores fill whole cache lines.
+__device__ __forceinline__ void sh_grad(const BwdViews& pk, const pvg_gaussians_grad& grad, int accumulate, int64_t i,
+                                        bool any) {
   const Scene& s = pk.views[0].s;
   const int64_t n = s.n;
+  const int K = (s.degree + 1) * (s.degree + 1);
+  // dL/dsh_k = Y_k(dir) d(rgb), where the colour is not clamped
+  float gsh[48];
+#pragma unroll
+  for (int j = 0; j < 48; ++j) gsh[j] = (j < 3 * K && accumulate) ? grad.sh[j * n + i] : 0.0f;
+  if (any) {
+    for (int v = 0; v < pk.nv; ++v) {
+      if (pk.radius[v][i] <= 0) continue;
+      if (pk.no_colour[v]) continue;
+      const float* g = pk.g2d[v] + kG2DStride * i;  // d(rgb) unclamped part and direction, from the first loop
+      if (pk.feat_grad[v]) {  // a feature view: its gradient goes to the feature rows, not to the SH
+        for (int c = 0; c < 3; ++c) pk.feat_grad[v][c * n + i] += g[6 + c];
+        continue;
+      }
+      const float draw[3] = {g[6], g[7], g[8]};
+      float Y[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) Y[k] = 0.0f;
+      sh_eval_basis(s.degree, g[9], g[10], g[11], Y);
+#pragma unroll
+      for (int j = 0; j < 48; ++j) gsh[j] += Y[j / 3] * draw[j % 3];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 48; ++j)
+    if (j < 3 * K) grad.sh[j * n + i] = gsh[j];
+}
+
+// Adjoint of the per-Gaussian stage for up to kMaxBwdViews views of one set
+// of Gaussians at one render time (the host splits passes where t changes):
+// each Gaussian's gradient is summed over the views (the SH part in a second
+// loop over the views, to bound register use) and written, or added, once.  A
+// Gaussian no view sees gets zeros (accumulate = 0) or is left alone.  Views
+// are summed pk.group at a time and the groups' chains added in turn, the
+// order of a pass per group.
+//
+// Bound: memory, the parameters in and the gradients out (1.56 GB each at 6M
+// Gaussians).  Zeros and values leave in the same stores: written by
+// themselves, the zeros' half-filled cache lines left L2 before the values
+// came and went to memory twice (2.1 to 2.9 GB at 6M, one view 1,152 us
+// against 891).  Taking all views in one pass, not one per three, reads
+// parameters and gradients once: a 6-view step at 6M 9,790 -> 9,280 us, at 1M
+// 4,340 -> 4,210, although a pass no longer runs beside the next views'
+// compositing.  Four waves a SIMD (a few spills) against three: one view at
+// 200k 34 us against 41, at 6M 870 against 947.
+__global__ void __launch_bounds__(256, 4) k_preprocess_bwd(BwdViews pk, pvg_gaussians_grad grad, int accumulate) {
+  const Scene& s = pk.views[0].s;
+  const int64_t n = s.n;
+  __shared__ float s_acc[sizeof(GeoGrad) / 4][256];
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (i >= n) return;
-  const int K = (s.degree + 1) * (s.degree + 1);
   bool any = false;
   for (int v = 0; v < pk.nv; ++v) any = any || pk.radius[v][i] > 0;
-  if (!any) {
-    if (!accumulate) {
-      for (int c = 0; c < 3; ++c) {
-        grad.mu[c * n + i] = 0.0f; grad.scale[c * n + i] = 0.0f; grad.vel[c * n + i] = 0.0f;
-      }
-      for (int c = 0; c < 4; ++c) grad.rot[c * n + i] = 0.0f;
-      for (int c = 0; c < 3 * K; ++c) grad.sh[c * n + i] = 0.0f;
-      grad.opacity[i] = 0.0f; grad.period[i] = 0.0f; grad.tau[i] = 0.0f; grad.beta[i] = 0.0f;
-    }
-    return;
-  }
-  GaussTime G;
-  gauss_time(s, i, pk.views[0].t, G);
-  GaussCov C;
-  C.ready = false;
-  ViewSums S;
-  for (int e = 0; e < 6; ++e) S.dSig[e] = 0.0f;
-  for (int c = 0; c < 3; ++c) S.dvb[c] = 0.0f;
-  S.drho = 0.0f;
-  clear_time_sums(S);
-  float dnorm = 0.0f, dcount = 0.0f;  // view-space gradient statistics of the adaptive control
-  for (int v = 0; v < pk.nv; ++v) {
-    if (pk.radius[v][i] <= 0) continue;
-    const View& vw = pk.views[v];
-    float* g = pk.g2d[v] + kG2DStride * i;
-    if (grad.densify_grad) {  // |dL / d(mean in NDC)|, NDC = 2 (pixel / size) - 1
-      const float gx = g[0] * (0.5f * static_cast<float>(vw.W));
-      const float gy = g[1] * (0.5f * static_cast<float>(vw.H));
-      dnorm += sqrtf(gx * gx + gy * gy);
-      dcount += 1.0f;
-    }
-    Proj P;
-    project_view(vw, i, G, C, P, false);
-    view_direction(vw, P);
-    adjoint_view(vw, i, P, C, pk.rgb[v] + 3 * i, g, S, pk.feat_grad[v] != nullptr || pk.no_colour[v]);
-  }
+  if (!any && accumulate) return;
   GeoGrad acc = {};
   if (accumulate) {  // start from the previous values
     for (int q = 0; q < 3; ++q) {
@@ -407,14 +428,51 @@ __global__ void __launch_bounds__(256) k_preprocess_bwd(BwdViews pk, pvg_gaussia
     acc.tau = grad.tau[i];
     acc.beta = grad.beta[i];
   }
-  adjoint_time(s, i, G, S, acc);
-  gauss_cov(s, i, C);  // formed again rather than held through the view loop
-  adjoint_cov(C, S.dSig, acc);
-  adjoint_features(G, S, acc);
-  if (grad.densify_grad) {
-    grad.densify_grad[i] += dnorm;
-    grad.densify_count[i] += dcount;
+  acc_out(acc, s_acc);
+  if (any) {
+    GaussTime G;
+    gauss_time(s, i, pk.views[0].t, G);
+    GaussCov C;
+    C.ready = false;
+    for (int v0 = 0; v0 < pk.nv; v0 += pk.group) {
+      ViewSums S;
+      for (int e = 0; e < 6; ++e) S.dSig[e] = 0.0f;
+      for (int c = 0; c < 3; ++c) S.dvb[c] = 0.0f;
+      S.drho = 0.0f;
+      clear_time_sums(S);
+      float dnorm = 0.0f, dcount = 0.0f;  // view-space gradient statistics of the adaptive control
+      bool seen = false;
+      for (int v = v0; v < min(v0 + pk.group, pk.nv); ++v) {
+        if (pk.radius[v][i] <= 0) continue;
+        seen = true;
+        const View& vw = pk.views[v];
+        float* g = pk.g2d[v] + kG2DStride * i;
+        if (grad.densify_grad) {  // |dL / d(mean in NDC)|, NDC = 2 (pixel / size) - 1
+          const float gx = g[0] * (0.5f * static_cast<float>(vw.W));
+          const float gy = g[1] * (0.5f * static_cast<float>(vw.H));
+          dnorm += sqrtf(gx * gx + gy * gy);
+          dcount += 1.0f;
+        }
+        Proj P;
+        project_view(vw, i, G, C, P, false);
+        view_direction(vw, P);
+        adjoint_view(vw, i, P, C, pk.rgb[v] + 3 * i, g, S, pk.feat_grad[v] != nullptr || pk.no_colour[v]);
+      }
+      if (!seen) continue;
+      GeoGrad sum;
+      acc_in(sum, s_acc);
+      adjoint_time(s, i, G, S, sum);
+      gauss_cov(s, i, C);  // formed again rather than held through the view loop
+      adjoint_cov(C, S.dSig, sum);
+      adjoint_features(G, S, sum);
+      acc_out(sum, s_acc);
+      if (grad.densify_grad) {
+        grad.densify_grad[i] += dnorm;
+        grad.densify_count[i] += dcount;
+      }
+    }
   }
+  acc_in(acc, s_acc);
   for (int q = 0; q < 3; ++q) {
     grad.mu[q * n + i] = acc.mu[q];
     grad.vel[q * n + i] = acc.vel[q];
@@ -425,30 +483,7 @@ __global__ void __launch_bounds__(256) k_preprocess_bwd(BwdViews pk, pvg_gaussia
   grad.period[i] = acc.l;
   grad.tau[i] = acc.tau;
   grad.beta[i] = acc.beta;
-
-  // dL/dsh_k = Y_k(dir) d(rgb), where the colour is not clamped
-  float gsh[48];
-#pragma unroll
-  for (int j = 0; j < 48; ++j) gsh[j] = (j < 3 * K && accumulate) ? grad.sh[j * n + i] : 0.0f;
-  for (int v = 0; v < pk.nv; ++v) {
-    if (pk.radius[v][i] <= 0) continue;
-    if (pk.no_colour[v]) continue;
-    const float* g = pk.g2d[v] + kG2DStride * i;  // d(rgb) unclamped part and direction, from the first loop
-    if (pk.feat_grad[v]) {  // a feature view: its gradient goes to the feature rows, not to the SH
-      for (int c = 0; c < 3; ++c) pk.feat_grad[v][c * n + i] += g[6 + c];
-      continue;
-    }
-    const float draw[3] = {g[6], g[7], g[8]};
-    float Y[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) Y[k] = 0.0f;
-    sh_eval_basis(s.degree, g[9], g[10], g[11], Y);
-#pragma unroll
-    for (int j = 0; j < 48; ++j) gsh[j] += Y[j / 3] * draw[j % 3];
-  }
-#pragma unroll
-  for (int j = 0; j < 48; ++j)
-    if (j < 3 * K) grad.sh[j * n + i] = gsh[j];
+  sh_grad(pk, grad, accumulate, i, any);
 }
 
 __global__ void k_fill_u32(uint32_t* p, uint32_t v, int64_t n) {

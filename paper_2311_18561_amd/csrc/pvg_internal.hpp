@@ -147,6 +147,7 @@ hipError_t launch_preprocess(const ViewSet& vs, const Geom& geom, hipStream_t s)
 constexpr int kMaxBwdViews = 8;
 struct BwdViews {
   int32_t nv;
+  int32_t group;  // views whose gradients are summed before the chain of what they share
   View views[kMaxBwdViews];
   const int32_t* radius[kMaxBwdViews];
   const float* rgb[kMaxBwdViews];  // the forward's colours (clamped channels are -0)
