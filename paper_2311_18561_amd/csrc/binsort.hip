@@ -615,6 +615,163 @@ __global__ void __launch_bounds__(kThreads) k_row_base(ViewSet vs, const uint32_
   }
 }
 
+// Steps 1 to 2 and the row offsets for few Gaussians, in one block: the
+// visible ones are compacted into LDS, sorted there by depth (8-bit passes;
+// one whose digit all keys share is left out) and written as `order`; with
+// culling their rows are counted, checked against the capacity and scanned as
+// by k_row_count to k_row_base.  One launch of 20 us at 2,000 Gaussians (31 at
+// 5,000) for twenty dependent ones of a few blocks each, some 4.5 us apart:
+// 128x96 and 2,000 Gaussians 194 -> 138 us a render.  Its bound is the chain
+// of a block's steps, so it loses where the passes' own work would fill many
+// blocks.
+constexpr int kSmallOrder = 8192;
+__global__ void __launch_bounds__(1024) k_order_small(ViewSet vs, Geom geom, int n, int cull, int64_t cap,
+                                                      uint32_t* counters, uint32_t* order, uint32_t* num_rows,
+                                                      uint32_t* row_off, uint32_t* row_base, uint32_t* starts) {
+  constexpr int kWaves = 16, kPer = kSmallOrder / 1024;
+  __shared__ uint32_t s_key[2][kSmallOrder];
+  __shared__ uint16_t s_idx[2][kSmallOrder];
+  __shared__ uint32_t s_cnt[kWaves][256];
+  __shared__ uint32_t s_w[kPer * kWaves];
+  __shared__ uint32_t lds[kWaves + 1];
+  __shared__ uint32_t s_or, s_and;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint64_t lt = (1ull << lane) - 1ull;
+  // compaction, in index order
+  if (tid == 0) { s_or = 0u; s_and = 0xffffffffu; }
+  uint64_t seen[kPer];
+  uint32_t key[kPer];
+#pragma unroll
+  for (int it = 0; it < kPer; ++it) {
+    const int i = 1024 * it + tid;
+    const bool f = i < n && geom.tiles[i] > 0u;
+    key[it] = f ? __float_as_uint(geom.depth[i]) : 0u;
+    seen[it] = __ballot(f);
+    if (lane == 0) s_w[kWaves * it + wid] = static_cast<uint32_t>(__popcll(seen[it]));
+  }
+  __syncthreads();
+  if (wid == 0) {
+    const uint32_t a = s_w[2 * lane], b = s_w[2 * lane + 1];
+    const uint32_t x = wave_incl_scan<uint32_t>(a + b, lane);
+    s_w[2 * lane] = x - a - b;
+    s_w[2 * lane + 1] = x - b;
+    if (lane == 63) lds[0] = x;
+  }
+  __syncthreads();
+  const int nv = static_cast<int>(lds[0]);
+  uint32_t any = 0u, all = 0xffffffffu;
+#pragma unroll
+  for (int it = 0; it < kPer; ++it) {
+    if (!(seen[it] >> lane & 1ull)) continue;
+    const uint32_t p = s_w[kWaves * it + wid] + static_cast<uint32_t>(__popcll(seen[it] & lt));
+    s_key[0][p] = key[it];
+    s_idx[0][p] = static_cast<uint16_t>(1024 * it + tid);
+    any |= key[it];
+    all &= key[it];
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    any |= __shfl_xor(any, off, 64);
+    all &= __shfl_xor(all, off, 64);
+  }
+  if (lane == 0) {
+    atomicOr(&s_or, any);
+    atomicAnd(&s_and, all);
+  }
+  __syncthreads();
+  const uint32_t differ = s_or & ~s_and;  // bits that not all keys share
+  const int its = ((nv + 63) / 64 + kWaves - 1) / kWaves;  // 64s per wave
+  int src = 0;
+  for (int shift = 0; shift < 32; shift += 8) {
+    if (!((differ >> shift) & 255u)) continue;
+    for (int q = tid; q < kWaves * 256; q += 1024) (&s_cnt[0][0])[q] = 0u;
+    __syncthreads();
+    uint32_t rank[kPer];
+    uint16_t idx[kPer];
+#pragma unroll
+    for (int it = 0; it < kPer; ++it) {
+      const int i = (wid * its + it) * 64 + lane;
+      rank[it] = 0xffffffffu;
+      if (it < its) {
+        const bool valid = i < nv;
+        key[it] = valid ? s_key[src][i] : 0u;
+        idx[it] = valid ? s_idx[src][i] : 0;
+        rank[it] = wave_rank((key[it] >> shift) & 255u, valid, 8, s_cnt[wid], lt);
+      }
+    }
+    __syncthreads();
+    uint32_t tot = 0;
+    if (tid < 256)
+      for (int w = 0; w < kWaves; ++w) tot += s_cnt[w][tid];
+    uint32_t sum;
+    uint32_t run = block_excl_scan<uint32_t, 1024>(tot, lds, sum);
+    if (tid < 256) {
+      for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = s_cnt[w][tid];
+        s_cnt[w][tid] = run;
+        run += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kPer; ++it) {
+      if (rank[it] == 0xffffffffu) continue;
+      const uint32_t p = s_cnt[wid][(key[it] >> shift) & 255u] + rank[it];
+      s_key[src ^ 1][p] = key[it];
+      s_idx[src ^ 1][p] = idx[it];
+    }
+    src ^= 1;
+    __syncthreads();
+  }
+  for (int k = tid; k < nv; k += 1024) order[k] = s_idx[src][k];
+  // rows in depth order, consecutive Gaussians to a thread
+  uint32_t rows[kPer], y0[kPer], mine = 0;
+  if (cull) {
+    const int per = (nv + 1023) / 1024;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int k = tid * per + q;
+      rows[q] = 0;
+      y0[q] = 0;
+      if (q < per && k < nv) {
+        float2 m;
+        int32_t rect[4];
+        rect_of(vs, geom.xy, geom.radius, s_idx[src][k], m, rect);
+        rows[q] = static_cast<uint32_t>(rect[3] - rect[1]);
+        y0[q] = static_cast<uint32_t>(rect[1]);
+        mine += rows[q];
+      }
+    }
+    uint32_t total;
+    uint32_t r0 = block_excl_scan<uint32_t, 1024>(mine, lds, total);
+    const bool over = static_cast<int64_t>(total) > cap;
+    if (tid == 0) {
+      *num_rows = over ? 0u : total;
+      counters[0] = 0u;
+      counters[1] = static_cast<uint32_t>(nv);
+      counters[2] = over ? 1u : 0u;
+      counters[3] = total;
+    }
+    if (over) return;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int k = tid * per + q;
+      if (q < per && k < nv) {
+        row_off[k] = r0;
+        if (row_base) row_base[s_idx[src][k]] = r0 - y0[q];
+        if (starts)
+          for (uint32_t b = (r0 + kRowSort - 1) / kRowSort; b * kRowSort < r0 + rows[q]; ++b) starts[b] = k;
+        r0 += rows[q];
+      }
+    }
+  } else if (tid == 0) {
+    counters[0] = 0u;
+    counters[1] = static_cast<uint32_t>(nv);
+    counters[2] = 0u;
+    counters[3] = 0u;
+  }
+}
+
 // One thread per rectangle row, 256 consecutive rows per block iteration.
 // The rows' owners (at most 256, consecutive in depth order) are found by a
 // wave search over row_off and staged in LDS with their ellipse.  Writes
@@ -1499,8 +1656,24 @@ int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp,
   const int64_t cap = plan.capacity;
   const int64_t nvis_stride = std::max<int64_t>(n, 1);
 
-  PVG_HIP(launch_fill_u32(counters, 0u, 4, s));
-  if (n > 0) {
+  const bool cull = bins->tile_cull != 0;
+  unsigned long long* partials2 = reinterpret_cast<unsigned long long*>(base + plan.off_partials2);
+  uint4* rows = reinterpret_cast<uint4*>(base + plan.off_rows);
+  uint32_t* num_rows = reinterpret_cast<uint32_t*>(base + plan.off_num_rows);
+  RowSort rs{};
+  const bool by_rows = plan_rows(vs, bins, reinterpret_cast<uint32_t*>(rows), rs);
+  // as many as one block's LDS holds: there the launches are the cost (a render at
+  // 320x208 of 1,000 Gaussians 182 -> 130 us, of 8,192 194 -> 157)
+  const bool small = n > 0 && n <= kSmallOrder && !vs.table;
+  if (small) {
+    StageScope sc(PVG_STAGE_DEPTH_SORT, s);
+    hipLaunchKernelGGL(k_order_small, dim3(1), dim3(1024), 0, s, vs, geom, static_cast<int>(n), cull ? 1 : 0, cap,
+                       counters, vvals, num_rows, offsets, bins->row_base, by_rows ? rs.starts : nullptr);
+    PVG_HIP(hipGetLastError());
+  } else {
+    PVG_HIP(launch_fill_u32(counters, 0u, 4, s));
+  }
+  if (n > 0 && !small) {
     StageScope sc(PVG_STAGE_COMPACT, s);
     const unsigned nb = static_cast<unsigned>(cdiv(n, kScanBlock));
     hipLaunchKernelGGL(k_vis_count, dim3(nb), dim3(kThreads), 0, s, geom.tiles, vs.live, n, partials);
@@ -1514,7 +1687,7 @@ int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp,
     PVG_HIP(hipGetLastError());
   }
   // depth sort of the visible Gaussians: kDepthPasses LSD passes, ending in buffer 0
-  if (n > 0) {
+  if (n > 0 && !small) {
     StageScope sc(PVG_STAGE_DEPTH_SORT, s);
     const auto depth_pass = radix_pass<kDepthBits, kDepthItems>;
     for (int pass = 0; pass < kDepthPasses; ++pass) {
@@ -1526,12 +1699,6 @@ int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp,
     }
   }
   const uint32_t* order = vvals;  // buffer 0 after the depth passes
-  const bool cull = bins->tile_cull != 0;
-  unsigned long long* partials2 = reinterpret_cast<unsigned long long*>(base + plan.off_partials2);
-  uint4* rows = reinterpret_cast<uint4*>(base + plan.off_rows);
-  uint32_t* num_rows = reinterpret_cast<uint32_t*>(base + plan.off_num_rows);
-  RowSort rs{};
-  const bool by_rows = plan_rows(vs, bins, reinterpret_cast<uint32_t*>(rows), rs);
   const unsigned nbv_max = static_cast<unsigned>(std::max<int64_t>(1, cdiv(n, kScanBlock)));
   // instance counts in depth order and the capacity check: rectangle tiles, or
   // (culled) rectangle rows, their reached intervals and the reached tiles
@@ -1544,16 +1711,18 @@ int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp,
                          static_cast<const int64_t*>(nullptr), n, kScanBlock, counters, cap, counters + 2,
                          counters + 3, static_cast<const uint32_t*>(nullptr));
     } else {
-      PVG_HIP(launch_fill_u32(num_rows, 0u, 1, s));
-      const unsigned nbr = static_cast<unsigned>(cdiv(n, kRowBlock));
       const unsigned nrb = static_cast<unsigned>(std::min(kMaxGrid, std::max<int64_t>(1, cdiv(cap, kRowBlock))));
-      hipLaunchKernelGGL(k_row_count, dim3(nbr), dim3(kThreads), 0, s, vs, order, geom.xy, geom.radius,
-                         counters + 1, n, partials);
-      hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partials, counters + 1,
-                         static_cast<const int64_t*>(nullptr), n, kRowBlock, num_rows, cap, counters + 2,
-                         counters + 3, static_cast<const uint32_t*>(nullptr));
-      hipLaunchKernelGGL(k_row_base, dim3(nbr), dim3(kThreads), 0, s, vs, order, geom.xy, geom.radius, counters + 1,
-                         n, partials, counters, offsets, bins->row_base, by_rows ? rs.starts : nullptr);
+      if (!small) {
+        PVG_HIP(launch_fill_u32(num_rows, 0u, 1, s));
+        const unsigned nbr = static_cast<unsigned>(cdiv(n, kRowBlock));
+        hipLaunchKernelGGL(k_row_count, dim3(nbr), dim3(kThreads), 0, s, vs, order, geom.xy, geom.radius,
+                           counters + 1, n, partials);
+        hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partials, counters + 1,
+                           static_cast<const int64_t*>(nullptr), n, kRowBlock, num_rows, cap, counters + 2,
+                           counters + 3, static_cast<const uint32_t*>(nullptr));
+        hipLaunchKernelGGL(k_row_base, dim3(nbr), dim3(kThreads), 0, s, vs, order, geom.xy, geom.radius, counters + 1,
+                           n, partials, counters, offsets, bins->row_base, by_rows ? rs.starts : nullptr);
+      }
       if (by_rows) {
         (rs.nrows <= 256 ? launch_row_keys<256> : launch_row_keys<1024>)(vs, rs, order, geom, offsets, num_rows, bins,
                                                                          partials2, s);

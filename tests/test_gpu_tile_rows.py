@@ -83,6 +83,40 @@ def test_lists(W, H, n, grow):
         assert not over.ranges.any()
 
 
+@pytest.mark.parametrize("n", [1, 63, 65, 1024, 1025, 3000, 8191, 8192, 8193])
+def test_few_gaussians(n):
+    """The one-block ordering up to 8,192 Gaussians, and one more: every third
+    Gaussian at the depth of another (ties go by index), both list forms, over
+    capacity, and nothing in view."""
+    from paper_2311_18561_amd import bin_sort, bin_sort_nosync
+    from paper_2311_18561_amd.render import camera_struct, frame_struct, preprocess
+    scene = gen.make_scene(n, n)
+    scene["mu"][:, ::3] = scene["mu"][:, :1]
+    for f in ("vel", "period", "tau"):
+        scene[f][..., ::3] = scene[f][..., :1]
+    W, H = 203, 119
+    for seen in (True, False):
+        cam = camera_struct(gen.make_camera(W, H))
+        if not seen:
+            cam.znear = 1e6
+        geom = preprocess(to_device(scene), n, 0, cam, frame_struct(0.5))
+        vis = np.flatnonzero(geom.radius.cpu().numpy() > 0)
+        assert seen or vis.size == 0
+        m = _check(geom, bin_sort(geom, cam), W, H)
+        assert _check(geom, bin_sort_nosync(geom, cam, 1 << 18), W, H) == m
+        if m > 1:
+            over = bin_sort_nosync(geom, cam, 1)
+            torch.cuda.synchronize()
+            assert not over.ranges.any() and int(over.counters[2]) == 1
+        rect = bin_sort(geom, cam, tile_cull=False)
+        torch.cuda.synchronize()
+        count = _u32(geom.tiles).astype(np.int64)
+        order = vis[np.argsort(geom.depth.cpu().numpy()[vis].view(np.uint32), kind="stable")]
+        first = np.cumsum(count[order]) - count[order]
+        assert int(rect.counters[1]) == vis.size and rect.num_listed() == count.sum()
+        assert np.array_equal(_u32(rect.first)[order], first.astype(np.uint32))
+
+
 def test_batch_of_many_rows():
     """A served batch of 365 tile rows of three widths equals the views rendered alone."""
     import paper_2311_18561_amd as pvg
