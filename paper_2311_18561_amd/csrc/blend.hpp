@@ -252,51 +252,80 @@ __device__ __forceinline__ uint32_t record_index(const Lists& lists, const Geom&
   return lists.first[g] + static_cast<uint32_t>((ty - rect[1]) * (rect[2] - rect[0]) + (tx - rect[0]));
 }
 
-// acc[q] += r[q], q < kSums; records of a multiple of four floats (the
-// record array 16-byte aligned) are read 16 bytes at a time.
+// Record r into x; records of a multiple of four floats (the record array
+// 16-byte aligned) are read 16 bytes at a time.
 template <int kSums>
-__device__ __forceinline__ void add_record(const float* __restrict__ r, float* acc) {
+__device__ __forceinline__ void load_record(const float* __restrict__ r, float (&x)[kSums]) {
   if constexpr (kSums % 4 == 0) {
 #pragma unroll
     for (int q = 0; q < kSums / 4; ++q) {
-      const float4 x = reinterpret_cast<const float4*>(r)[q];
-      acc[4 * q] += x.x;
-      acc[4 * q + 1] += x.y;
-      acc[4 * q + 2] += x.z;
-      acc[4 * q + 3] += x.w;
+      const float4 v = reinterpret_cast<const float4*>(r)[q];
+      x[4 * q] = v.x;
+      x[4 * q + 1] = v.y;
+      x[4 * q + 2] = v.z;
+      x[4 * q + 3] = v.w;
     }
   } else {
 #pragma unroll
-    for (int q = 0; q < kSums; ++q) acc[q] += r[q];
+    for (int q = 0; q < kSums; ++q) x[q] = r[q];
   }
 }
+// acc[q] += r[q], q < kSums.
+template <int kSums>
+__device__ __forceinline__ void add_record(const float* __restrict__ r, float* acc) {
+  float x[kSums];
+  load_record<kSums>(r, x);
+#pragma unroll
+  for (int q = 0; q < kSums; ++q) acc[q] += x[q];
+}
 
-// Sum of one Gaussian's flagged records in [e0, e0 + cnt) by one thread,
-// reading the flags 16 at a time.  The emission order keeps a Gaussian's
-// pairs contiguous.
+constexpr uint32_t kShortRange = 48;  // Gaussians with more listed pairs are gathered by a whole wave
+
+// Sum of one Gaussian's flagged records in [e0, e0 + cnt), cnt <= kShortRange,
+// by one thread, in emission order (which keeps a Gaussian's pairs
+// contiguous).  The flags (bytes of 0 or 1) become one bit mask, so a wave
+// takes as many steps as its fullest Gaussian has flagged records (about an
+// eighth of the listed), each with the next record already on its way.  A step
+// per listed pair, each waiting for its record: the gather of a 6M view 170 us
+// against 155, of 20 feature channels at 1M 152 against 130.
 // kAcc (>= kSums) is the width of acc, which is cleared first.
 template <int kSums, int kAcc = 16>
 __device__ __forceinline__ void gather_range(uint32_t e0, uint32_t cnt, const float* __restrict__ rec,
                                              const uint8_t* __restrict__ vis, float acc[kAcc]) {
   static_assert(kSums <= kAcc, "accumulator narrower than a record");
+  static_assert(kShortRange + 15 < 64, "the mask holds a range from its 16-byte boundary on");
 #pragma unroll
   for (int c = 0; c < kAcc; ++c) acc[c] = 0.0f;
-  const uint32_t e1 = e0 + cnt;
-  for (uint32_t b = e0 & ~15u; b < e1; b += 16) {
-    const uint4 w = *reinterpret_cast<const uint4*>(vis + b);
-    const uint32_t words[4] = {w.x, w.y, w.z, w.w};
+  const uint32_t b = e0 & ~15u, e1 = e0 + cnt;
+  uint64_t bits = 0;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const uint32_t e = b + static_cast<uint32_t>(j);
-      if (((words[j >> 2] >> (8 * (j & 3))) & 0xffu) && e >= e0 && e < e1) {
-        const float* r = rec + kSums * static_cast<int64_t>(e);  // records are kSums floats apart
-        add_record<kSums>(r, acc);
-      }
+  for (int q = 0; q < 4; ++q) {
+    if (b + 16 * q < e1) {
+      const uint4 w = *reinterpret_cast<const uint4*>(vis + b + 16 * q);
+      // the four bytes' low bits side by side in bits 24 .. 27
+      const uint32_t m = ((w.x * 0x01020408u) >> 24 & 15u) | ((w.y * 0x01020408u) >> 24 & 15u) << 4 |
+                         ((w.z * 0x01020408u) >> 24 & 15u) << 8 | ((w.w * 0x01020408u) >> 24 & 15u) << 12;
+      bits |= static_cast<uint64_t>(m) << (16 * q);
     }
+  }
+  bits &= (1ull << (e1 - b)) - 1ull;
+  bits &= ~0ull << (e0 - b);
+  if (!bits) return;
+  float x[kSums];
+  load_record<kSums>(rec + kSums * static_cast<int64_t>(b + __ffsll(static_cast<unsigned long long>(bits)) - 1), x);
+  for (;;) {
+    bits &= bits - 1;
+    float next[kSums];
+    if (bits)
+      load_record<kSums>(rec + kSums * static_cast<int64_t>(b + __ffsll(static_cast<unsigned long long>(bits)) - 1), next);
+#pragma unroll
+    for (int q = 0; q < kSums; ++q) acc[q] += x[q];
+    if (!bits) break;
+#pragma unroll
+    for (int q = 0; q < kSums; ++q) x[q] = next[q];
   }
 }
 
-constexpr uint32_t kShortRange = 48;  // Gaussians with more listed pairs are gathered by a whole wave
 // Gaussians with more listed pairs than this (near-camera splats reach most
 // of the frame's 9,600 tiles, and a splat in front is flagged in nearly all of
 // them) are gathered by the whole block, each wave taking every fourth
