@@ -159,6 +159,37 @@ __device__ __forceinline__ void group_sum_store(const float (&h)[kN][2], int lan
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The same for two pairs: h[q] holds sum q of pair 0 in lanes 0 .. 31 and of
+// pair 1 in lanes 32 .. 63.  Each (sum, pair) is a row of 32 in LDS, which one
+// lane adds in the order of the DPP form's folds (lane ^ 16, ^ 8, ^ 4, ^ 2, ^ 1).
+// dst[stride u + q] receives sum q of pair u, with wave_sum_store's gap.
+constexpr int kPairStride = 36;
+template <int kN, int kSplit, int kGap>
+__device__ __forceinline__ void pair_sum_store(const float (&h)[kN], int lane, float* red, float* dst, int stride) {
+  const int u = lane >> 5;
+#pragma unroll
+  for (int q = 0; q < kN; ++q) red[(2 * q + u) * kPairStride + (lane & 31)] = h[q];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  for (int row = lane; row < 2 * kN; row += 64) {
+    const float4* r = reinterpret_cast<const float4*>(red + row * kPairStride);
+    float4 a[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 x = r[i], y = r[i + 4];
+      a[i] = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+    }
+    const float4 e = make_float4((a[0].x + a[2].x) + (a[1].x + a[3].x), (a[0].y + a[2].y) + (a[1].y + a[3].y),
+                                 (a[0].z + a[2].z) + (a[1].z + a[3].z), (a[0].w + a[2].w) + (a[1].w + a[3].w));
+    const int q = row >> 1;
+    dst[stride * (row & 1) + (q < kSplit ? q : q + kGap)] = (e.x + e.z) + (e.y + e.w);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ int wave_max(int x) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) x = max(x, __shfl_xor(x, off, 64));
