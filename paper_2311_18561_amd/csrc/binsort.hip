@@ -587,7 +587,7 @@ __global__ void __launch_bounds__(kThreads) k_row_base(ViewSet vs, const uint32_
                                                        int64_t n_host,
                                                        const unsigned long long* __restrict__ row_partials,
                                                        const uint32_t* __restrict__ counters, uint32_t* row_off,
-                                                       uint32_t* row_base, uint32_t* starts) {
+                                                       uint32_t* row_base, uint32_t* starts, int64_t nstarts) {
   __shared__ unsigned long long lds[5];
   if (counters[2]) return;
   const int64_t n = live_count(n_dev, n_host);
@@ -609,7 +609,9 @@ __global__ void __launch_bounds__(kThreads) k_row_base(ViewSet vs, const uint32_
     if (starts) {
       const uint32_t b = static_cast<uint32_t>((r0 + kRowSort - 1) / kRowSort);
       const uint64_t end = r0 + static_cast<uint32_t>(rect[3] - rect[1]);
-      for (uint64_t q = b; q * kRowSort < end; ++q) starts[q] = static_cast<uint32_t>(k);
+      // (the bound only matters for records that changed since k_row_count)
+      for (uint64_t q = b; q * kRowSort < end && static_cast<int64_t>(q) < nstarts; ++q)
+        starts[q] = static_cast<uint32_t>(k);
     }
     if (row_base) row_base[g] = static_cast<uint32_t>(r0) - static_cast<uint32_t>(rect[1]);
   }
@@ -1012,10 +1014,13 @@ __global__ void __launch_bounds__(kRowSort) k_row_keys(ViewSet vs, const uint32_
     for (int d = tid; d < nrows; d += kRowSort) s_h[d] = 0;
     if (tid < kRowSort / 32) s_mark[tid] = 0;
     __syncthreads();
-    // the block's owners: up to the next block's first, which may own rows of both
-    const int64_t k0 = starts[blk];
-    const int64_t k1 = blk + 1 < nblocks ? static_cast<int64_t>(starts[blk + 1]) : nvis - 1;
-    const int cnt = static_cast<int>(min<int64_t>(kRowSort, k1 - k0 + 1));
+    // the block's owners: up to the next block's first, which may own rows of
+    // both.  Records that changed since k_row_count may have left any value in
+    // starts and in the rectangles: the bounds here and on ty keep such input
+    // to wrong lists.
+    const int64_t k0 = min<int64_t>(starts[blk], nvis - 1);
+    const int64_t k1 = blk + 1 < nblocks ? min<int64_t>(starts[blk + 1], nvis - 1) : nvis - 1;
+    const int cnt = static_cast<int>(max<int64_t>(1, min<int64_t>(kRowSort, k1 - k0 + 1)));
     if (tid < cnt) {
       const uint32_t g = order[k0 + tid];
       float2 m;
@@ -1046,7 +1051,7 @@ __global__ void __launch_bounds__(kRowSort) k_row_keys(ViewSet vs, const uint32_
       const int4 ry = s_y[lo];
       const int ty = ry.x + static_cast<int>(ui - s_off[lo]);
       int c0 = 0, c1 = -1;
-      if (ty < ry.y) reach_row(s_rr[lo], ty, ry.z, s_x[lo].x, s_x[lo].y, c0, c1);
+      if (ty >= ry.x && ty < ry.y) reach_row(s_rr[lo], ty, ry.z, s_x[lo].x, s_x[lo].y, c0, c1);
       len = c1 >= c0 ? static_cast<uint32_t>(c1 - c0 + 1) : 0u;
       const uint32_t y = static_cast<uint32_t>(ry.w + ty);
       keys[i] = (y << 16) | (len ? static_cast<uint32_t>(c1) << 8 : 255u << 8) | static_cast<uint32_t>(c0);
@@ -1721,7 +1726,7 @@ int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp,
                            static_cast<const int64_t*>(nullptr), n, kRowBlock, num_rows, cap, counters + 2,
                            counters + 3, static_cast<const uint32_t*>(nullptr));
         hipLaunchKernelGGL(k_row_base, dim3(nbr), dim3(kThreads), 0, s, vs, order, geom.xy, geom.radius, counters + 1,
-                           n, partials, counters, offsets, bins->row_base, by_rows ? rs.starts : nullptr);
+                           n, partials, counters, offsets, bins->row_base, by_rows ? rs.starts : nullptr, rs.cols);
       }
       if (by_rows) {
         (rs.nrows <= 256 ? launch_row_keys<256> : launch_row_keys<1024>)(vs, rs, order, geom, offsets, num_rows, bins,
