@@ -71,13 +71,11 @@ def stage_bytes(stage, n, n_vis, M, Lst, visited, K, tiles, tile_passes, views=1
     if stage == "depth_sort":
         return 4 * 16 * n_vis
     if stage == "scan_emit":
-        # tile counts and offsets, each owner's record read by the count and
-        # the write pass, and the listed instances written
-        return n_vis * 16 + 2 * n_vis * 36 + Lst * 8
+        # each owner's record read by the count and the interval pass, and its
+        # row offset (the row records, 8 B a row, are not counted)
+        return n_vis * 16 + 2 * n_vis * 36
     if stage == "tile_sort":
-        return tile_passes * 16 * Lst
-    if stage == "ranges":
-        return Lst * 4 + tiles * 8
+        return Lst * 8 + tiles * 8  # the finished lists and ranges, written once from the row records
     if stage == "grad_gather":
         # per visible Gaussian its record (40 B) in and nine sums out, the cut keys, the visited records
         return n * 4 + n_vis * (40 + 36) + tiles * 8 + visited * 36
