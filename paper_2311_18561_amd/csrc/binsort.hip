@@ -618,22 +618,24 @@ __global__ void __launch_bounds__(kThreads) k_row_base(ViewSet vs, const uint32_
 }
 
 // Steps 1 to 2 and the row offsets for few Gaussians, in one block: the
-// visible ones are compacted into LDS, sorted there by depth (8-bit passes;
-// one whose digit all keys share is left out) and written as `order`; with
-// culling their rows are counted, checked against the capacity and scanned as
-// by k_row_count to k_row_base.  One launch of 20 us at 2,000 Gaussians (31 at
-// 5,000) for twenty dependent ones of a few blocks each, some 4.5 us apart:
-// 128x96 and 2,000 Gaussians 194 -> 138 us a render.  Its bound is the chain
-// of a block's steps, so it loses where the passes' own work would fill many
-// blocks.
+// visible ones are compacted into LDS, sorted there by depth (over the bits
+// that differ between keys, in equal digits of at most nine: three passes for
+// depths within a factor of 2^16) and written as `order`; with culling their
+// rows are counted, checked against the capacity and scanned as by k_row_count
+// to k_row_base.  One launch of 16 us at 2,000 Gaussians (26 at 5,000) for
+// twenty dependent ones of a few blocks each, some 4.5 us apart: 320x208 and
+// 2,000 Gaussians 190 -> 129 us a render.  Its bound is the chain of a block's
+// steps (four passes of 8 bits: 20 and 31 us), so it loses where the passes'
+// own work would fill many blocks.
 constexpr int kSmallOrder = 8192;
 __global__ void __launch_bounds__(1024) k_order_small(ViewSet vs, Geom geom, int n, int cull, int64_t cap,
                                                       uint32_t* counters, uint32_t* order, uint32_t* num_rows,
                                                       uint32_t* row_off, uint32_t* row_base, uint32_t* starts) {
   constexpr int kWaves = 16, kPer = kSmallOrder / 1024;
+  constexpr int kBits = 9, kDigits = 1 << kBits;
   __shared__ uint32_t s_key[2][kSmallOrder];
   __shared__ uint16_t s_idx[2][kSmallOrder];
-  __shared__ uint32_t s_cnt[kWaves][256];
+  __shared__ uint32_t s_cnt[kWaves][kDigits];
   __shared__ uint32_t s_w[kPer * kWaves];
   __shared__ uint32_t lds[kWaves + 1];
   __shared__ uint32_t s_or, s_and;
@@ -683,10 +685,14 @@ __global__ void __launch_bounds__(1024) k_order_small(ViewSet vs, Geom geom, int
   __syncthreads();
   const uint32_t differ = s_or & ~s_and;  // bits that not all keys share
   const int its = ((nv + 63) / 64 + kWaves - 1) / kWaves;  // 64s per wave
+  // the bits from the lowest to the highest that differ, in equal digits of at
+  // most kBits
+  const int low = differ ? __ffs(differ) - 1 : 0, width = differ ? 32 - __clz(differ) - low : 0;
+  const int bits = width ? (width + (width + kBits - 1) / kBits - 1) / ((width + kBits - 1) / kBits) : 1;
+  const uint32_t mask = (1u << bits) - 1u;
   int src = 0;
-  for (int shift = 0; shift < 32; shift += 8) {
-    if (!((differ >> shift) & 255u)) continue;
-    for (int q = tid; q < kWaves * 256; q += 1024) (&s_cnt[0][0])[q] = 0u;
+  for (int shift = low; shift < low + width; shift += bits) {
+    for (int q = tid; q < kWaves * kDigits; q += 1024) (&s_cnt[0][0])[q] = 0u;
     __syncthreads();
     uint32_t rank[kPer];
     uint16_t idx[kPer];
@@ -698,16 +704,16 @@ __global__ void __launch_bounds__(1024) k_order_small(ViewSet vs, Geom geom, int
         const bool valid = i < nv;
         key[it] = valid ? s_key[src][i] : 0u;
         idx[it] = valid ? s_idx[src][i] : 0;
-        rank[it] = wave_rank((key[it] >> shift) & 255u, valid, 8, s_cnt[wid], lt);
+        rank[it] = wave_rank((key[it] >> shift) & mask, valid, bits, s_cnt[wid], lt);
       }
     }
     __syncthreads();
     uint32_t tot = 0;
-    if (tid < 256)
+    if (tid < kDigits)
       for (int w = 0; w < kWaves; ++w) tot += s_cnt[w][tid];
     uint32_t sum;
     uint32_t run = block_excl_scan<uint32_t, 1024>(tot, lds, sum);
-    if (tid < 256) {
+    if (tid < kDigits) {
       for (int w = 0; w < kWaves; ++w) {
         const uint32_t c = s_cnt[w][tid];
         s_cnt[w][tid] = run;
@@ -718,7 +724,7 @@ __global__ void __launch_bounds__(1024) k_order_small(ViewSet vs, Geom geom, int
 #pragma unroll
     for (int it = 0; it < kPer; ++it) {
       if (rank[it] == 0xffffffffu) continue;
-      const uint32_t p = s_cnt[wid][(key[it] >> shift) & 255u] + rank[it];
+      const uint32_t p = s_cnt[wid][(key[it] >> shift) & mask] + rank[it];
       s_key[src ^ 1][p] = key[it];
       s_idx[src ^ 1][p] = idx[it];
     }
@@ -1668,7 +1674,7 @@ int run_bin_sort(const ViewSet& vs, const Geom& geom, pvg_bins* bins, void* tmp,
   RowSort rs{};
   const bool by_rows = plan_rows(vs, bins, reinterpret_cast<uint32_t*>(rows), rs);
   // as many as one block's LDS holds: there the launches are the cost (a render at
-  // 320x208 of 1,000 Gaussians 182 -> 130 us, of 8,192 194 -> 157)
+  // 320x208 of 1,000 Gaussians 182 -> 125 us, of 8,192 194 -> 149)
   const bool small = n > 0 && n <= kSmallOrder && !vs.table;
   if (small) {
     StageScope sc(PVG_STAGE_DEPTH_SORT, s);

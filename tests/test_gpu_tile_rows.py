@@ -117,6 +117,26 @@ def test_few_gaussians(n):
         assert np.array_equal(_u32(rect.first)[order], first.astype(np.uint32))
 
 
+@pytest.mark.parametrize("spread", [0.0, 1e-6, 1.0, 1e9])
+def test_few_gaussians_of_any_depth_range(spread):
+    """The one-block sort's digits cover the bits that differ: none, the
+    lowest few, the usual three digits, and four."""
+    from paper_2311_18561_amd import bin_sort
+    from paper_2311_18561_amd.render import camera_struct, frame_struct, preprocess
+    n, W, H = 700, 203, 119
+    scene = gen.make_scene(n, 3)
+    scene["vel"][:] = 0.0
+    grow = np.exp(np.random.default_rng(4).uniform(0.0, np.log1p(spread), size=n))
+    scene["mu"] = np.float32([[0.1], [0.2], [4.0]]) * grow.astype(np.float32)
+    scene["scale"] *= grow.astype(np.float32)
+    geom = preprocess(to_device(scene), n, 0, camera_struct(gen.make_camera(W, H)), frame_struct(0.5))
+    depth = geom.depth.cpu().numpy()[geom.radius.cpu().numpy() > 0].view(np.uint32)
+    differ = int(np.bitwise_or.reduce(depth) & ~np.bitwise_and.reduce(depth))
+    width = differ.bit_length() - ((differ & -differ).bit_length() - 1) if differ else 0
+    assert {0.0: width == 0, 1e-6: 0 < width <= 9, 1.0: 18 < width <= 27, 1e9: width > 27}[spread]
+    _check(geom, bin_sort(geom, camera_struct(gen.make_camera(W, H))), W, H)
+
+
 def test_batch_of_many_rows():
     """A served batch of 365 tile rows of three widths equals the views rendered alone."""
     import paper_2311_18561_amd as pvg
