@@ -60,7 +60,7 @@ def parse():
     return ap.parse_args()
 
 
-def stage_bytes(stage, n, n_vis, M, Lst, visited, K, tiles, tile_passes, views=1):
+def stage_bytes(stage, n, n_vis, M, Lst, visited, K, tiles, views=1):
     """Algorithmic HBM bytes of one invocation of a stage.  M: rectangle
     instances, Lst: listed (culled) instances, visited: (Gaussian, tile)
     records the adjoint writes and the gather reads."""
@@ -805,7 +805,6 @@ def main():
     lmax = torch.nn.functional.pad(nc, (0, GXt * 16 - W, 0, GYt * 16 - H)).reshape(GYt, 16, GXt, 16)
     lmax = lmax.amax(dim=(1, 3)).reshape(-1).long()
     visited = int(torch.minimum(lmax, rng[:, 1] - rng[:, 0]).sum().item())
-    tile_passes = (max(1, (tiles - 1).bit_length()) + 7) // 8
     table = {}
     for name, st in stages.items():
         if st["calls"] == 0:
@@ -818,7 +817,7 @@ def main():
             row.update(bound="alu", pairs_per_call=pairs,
                        tflops=pairs * FLOPS_PER_PAIR[name] / (per_launch_ms * 1e-3) / 1e12)
         else:
-            b = stage_bytes(name, N, n_vis, M, Lst, visited, K, tiles, tile_passes, views=1)
+            b = stage_bytes(name, N, n_vis, M, Lst, visited, K, tiles, views=1)
             row.update(bound="hbm", bytes_per_call=b, gbs=b / (per_launch_ms * 1e-3) / 1e9)
         table[name] = row
     dom = max((k for k in table if k in SINGLE_KERNEL), key=lambda k: table[k]["ms_per_step"])
