@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "pvg_internal.hpp"
+#include "view_queue.hpp"
 
 namespace pvg {
 
@@ -566,21 +567,16 @@ int pvg_render_bwd_views_channels(const pvg_gaussians* g, int32_t n_views, const
   // a render time up to the slots' number; it sums them by groups of one view
   // per side stream.  The side streams wait for the caller's stream only when
   // slots are reused.
-  const int32_t group = serial ? kMaxBwdViews : regions;
-  int32_t used_slots = 0;
-  auto flush = [&]() -> int {
-    if (pk.nv == 0) return PVG_OK;
+  ViewQueue queue{kMaxBwdViews, serial ? kMaxBwdViews : regions};
+  pk.group = queue.group;
+  auto flush = [&](bool pending) -> int {
+    if (queue.queued == 0) return PVG_OK;
     int st = join();
     if (st != PVG_OK) return st;
-    pk.group = group;
+    pk.nv = queue.queued;
     PVG_HIP(launch_preprocess_bwd(pk, *grad, first_group ? accumulate : 1, s));
     first_group = false;
-    pk.nv = 0;
-    if (used_slots == kMaxBwdViews) {  // the next views reuse the slots this pass read
-      used_slots = 0;
-      return fork();
-    }
-    return PVG_OK;
+    return queue.passed(pending) ? fork() : PVG_OK;
   };
   {
     const int st = fork();
@@ -612,8 +608,7 @@ int pvg_render_bwd_views_channels(const pvg_gaussians* g, int32_t n_views, const
         return PVG_ERR_INVALID;
       }
     }
-    float* g2d = reinterpret_cast<float*>(base + slot_bytes * static_cast<size_t>(used_slots));
-    ++used_slots;
+    float* g2d = reinterpret_cast<float*>(base + slot_bytes * static_cast<size_t>(queue.take()));
     const int32_t r = launched % regions;
     char* region = base + off_rec + region_bytes * static_cast<size_t>(r);
     float* rec = reinterpret_cast<float*>(region);
@@ -623,22 +618,22 @@ int pvg_render_bwd_views_channels(const pvg_gaussians* g, int32_t n_views, const
     PVG_HIP(launch_render_bwd(single(v, g->n), to_geom(&geoms[k]), lists, rec, vis,
                               static_cast<int64_t>(vis_bytes), g2d, serial ? s : side[r]));
     ++launched;
-    if (pk.nv > 0 && !(v.t == pk.views[0].t)) {  // a pass shares one render time
-      const int st = flush();
+    if (queue.queued > 0 && !(v.t == pk.views[0].t)) {  // a pass shares one render time
+      const int st = flush(true);
       if (st != PVG_OK) return st;
     }
-    pk.views[pk.nv] = v;
-    pk.radius[pk.nv] = geoms[k].radius;
-    pk.rgb[pk.nv] = geoms[k].rgb;
-    pk.g2d[pk.nv] = g2d;
-    pk.feat_grad[pk.nv] = channels ? channels[k].feature_grad : nullptr;
-    ++pk.nv;
-    if (used_slots == kMaxBwdViews) {
-      const int st = flush();
+    const int32_t q = queue.queued++;
+    pk.views[q] = v;
+    pk.radius[q] = geoms[k].radius;
+    pk.rgb[q] = geoms[k].rgb;
+    pk.g2d[q] = g2d;
+    pk.feat_grad[q] = channels ? channels[k].feature_grad : nullptr;
+    if (queue.full()) {
+      const int st = flush(false);
       if (st != PVG_OK) return st;
     }
   }
-  const int st = flush();
+  const int st = flush(false);
   if (st != PVG_OK) return st;
   if (first_group && !accumulate && g->n > 0) return zero_param_grads(g, grad, s);
   return PVG_OK;
