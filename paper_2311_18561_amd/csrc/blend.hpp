@@ -237,10 +237,20 @@ constexpr int kPix = 4;  // pixels per lane
 constexpr int kGroup = 4;
 __device__ __forceinline__ int pad_to(int cnt) { return (cnt + kGroup - 1) / kGroup * kGroup; }
 
+// A range [e0, e0 + cnt) that does not lie inside the record slots becomes the
+// empty one at 0, as does an empty one: the gathers read the flags 16 at a
+// time from e0's 16-byte boundary on while it is below the range's end, which
+// for an empty range at another index is one read there.
+__host__ __device__ __forceinline__ void clip_range(uint32_t& e0, uint32_t& cnt, int64_t capacity) {
+  const uint64_t cap = static_cast<uint64_t>(capacity);
+  if (cnt == 0 || static_cast<uint64_t>(e0) > cap || static_cast<uint64_t>(cnt) > cap - e0) e0 = cnt = 0;
+}
+
 // The index range [e0, e0 + cnt) of a visible Gaussian's pairs in emission
 // order: first[g] and the listed count (its rectangle's tiles, or, for
 // culled lists, up to the end of its last row).  Lists of an overflowed sort
-// hold nothing; a range outside the record slots comes back empty.
+// hold nothing, and first[] and rows are then whatever memory held; a range
+// outside the record slots comes back empty.
 template <bool kCulled>
 __device__ __forceinline__ void record_range(const ViewSet& vs, const Geom& geom, const Lists& lists, int64_t gi,
                                              uint32_t& e0, uint32_t& cnt) {
@@ -259,8 +269,7 @@ __device__ __forceinline__ void record_range(const ViewSet& vs, const Geom& geom
   } else {
     cnt = geom.tiles[gi];
   }
-  const uint64_t cap = static_cast<uint64_t>(lists.capacity);
-  if (static_cast<uint64_t>(e0) > cap || static_cast<uint64_t>(cnt) > cap - e0) cnt = 0;
+  clip_range(e0, cnt, lists.capacity);
 }
 
 // Emission-order index of the pair (Gaussian g with 2D mean m, tile (tx,
