@@ -238,6 +238,34 @@ __device__ __forceinline__ void reach_row(const ReachRows& r, int ty, int H, int
   hi = static_cast<int>(th);
 }
 
+// tile_reachable for any sample rectangle, with the bounds of the row
+// intervals: the form's minimum is that of the conic shrunk by k I, so that a
+// pair is left out only if every pixel's exponent, as computed, skips it
+// (tile_reachable's 0.1% does not cover the rounding of that exponent for
+// splats some hundred times longer than wide).  A conic too close to singular
+// for that reaches everything.  Reciprocals and logarithm are the hardware's:
+// the first only place the points at which the form is evaluated, a few ulps
+// from the minimum, where it is flat, and the second is within the margin of
+// 0.01 by far.
+__device__ __forceinline__ bool rect_reachable(float gx, float gy, float A, float B, float C, float op, float X0,
+                                               float X1, float Y0, float Y1) {
+  if (!(isfinite(gx) && isfinite(gy) && isfinite(A) && isfinite(B) && isfinite(C) && isfinite(op))) return true;
+  if (op < kAlphaMin) return false;
+  const float k = 1e-5f * (fabsf(A) + fabsf(C) + 2.0f * fabsf(B));
+  const float a = A - k, c = C - k;
+  if (!(a > 0.0f && c > 0.0f && a * c - B * B > 0.0f)) return true;
+  const float dxl = gx - X1, dxh = gx - X0, dyl = gy - Y1, dyh = gy - Y0;
+  if (dxl <= 0.0f && dxh >= 0.0f && dyl <= 0.0f && dyh >= 0.0f) return true;
+  const float sy = -B * __builtin_amdgcn_rcpf(c), sx = -B * __builtin_amdgcn_rcpf(a);
+  auto q = [&](float dx, float dy) { return fmaf(c * dy, dy, fmaf(a * dx, dx, (2.0f * B * dx) * dy)); };
+  auto best_dy = [&](float dx) { return fminf(fmaxf(sy * dx, dyl), dyh); };
+  auto best_dx = [&](float dy) { return fminf(fmaxf(sx * dy, dxl), dxh); };
+  const float qmin =
+      fminf(fminf(q(dxl, best_dy(dxl)), q(dxh, best_dy(dxh))), fminf(q(best_dx(dyl), dyl), q(best_dx(dyh), dyh)));
+  const float need = 0.693147181f * __builtin_amdgcn_logf(op * 255.0f);
+  return !(0.5f * qmin * 0.999f > need + 0.01f);
+}
+
 // Sample rectangle [X0, X1] x [Y0, Y1] of tile (tx, ty) in a W x H image.
 __device__ __forceinline__ void tile_bounds(int tx, int ty, int W, int H, float& X0, float& X1, float& Y0, float& Y1) {
   X0 = static_cast<float>(tx * kTile);

@@ -33,9 +33,13 @@ namespace pvg {
 // bound).  The chip has 1,024 SIMDs and a wave alone issues at about a third
 // of a SIMD's rate, so a launch needs several waves a SIMD; a split tile
 // walks its list once per strip, which costs the per-pair work again.
-// Whole tiles / halves / quarters, us: 48 tiles 19.8 / 12.6 / 9.6, 117 tiles
-// 25.6 / 16.0 / 12.0, 2,400 tiles 66.6 / 55.1 / 59.6, 9,600 tiles 136.5 /
-// 140.2 / 165.6.
+// The lines lie where rectangle lists, whose strips also pay the tile test,
+// break even; culled lists gain from a split for a while longer.  us, 20,000 /
+// 200,000 Gaussians of a box:
+//   117 tiles, whole - halves - quarters: culled 103 - 56 - 40 / 73 - 43 - 31
+//   1,024 tiles, halves - quarters: culled 45 - 39 / 39 - 36, rectangles 51 - 53 / 51 - 52
+//   4,096 tiles, whole - halves: culled 84 - 75 / 78 - 74, rectangles 95 - 97 / 94 - 99
+//   8,160 tiles, whole - halves: culled 120 - 119 / 119 - 121, rectangles 146 - 157 / 142 - 159
 static int forward_parts(int64_t tiles) { return tiles <= 1024 ? 4 : tiles <= 4096 ? 2 : 1; }
 
 // Pairs per group of the walk: enough independent work for a lane with one
@@ -48,13 +52,17 @@ constexpr int forward_group(int px) { return px == 1 ? 8 : 4; }
 // kPx: pixels per lane.  A wave takes kPx / 4 of a tile, a strip of 4 kPx of
 // its rows (forward_parts has the rule): block b is strip b mod (4 / kPx) of
 // its tile, and each wave walks the tile's list by itself.
-// kTest: drop listed Gaussians that cannot reach the strip (rectangle lists,
-// and the strips of split tiles); otherwise every listed one is walked.
-template <bool kCount, bool kTest, bool kCh, int kPx>
+// Of rectangle lists (kCulled false) only the Gaussians that the tile test
+// keeps are walked, as in the adjoint and the feature kernels.  A strip also
+// leaves out those that cannot reach it, by rect_reachable: the adjoint walks
+// whole tiles, so a pair left out here that a pixel would use is divided out
+// of T there and credited with a gradient.
+template <bool kCount, bool kCulled, bool kCh, int kPx>
 __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const uint32_t* __restrict__ vals,
                                                    const uint32_t* __restrict__ ranges,
                                                    unsigned long long* pair_counter) {
   constexpr int kParts = 4 / kPx;
+  constexpr bool kTest = !kCulled || kParts > 1;  // not every listed Gaussian is walked
   constexpr int kGroup = forward_group(kPx);
   __shared__ float2 s_xy[64];
   __shared__ float4 s_co[64];
@@ -74,8 +82,9 @@ __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const 
   const int px = tx * kTile + (lane & 15);
   const int py0 = row0 + (lane >> 4);
   const float fpx = static_cast<float>(px);
-  const float X0 = static_cast<float>(tx * kTile), X1 = static_cast<float>(min(v.W, (tx + 1) * kTile) - 1);
-  const float Y0 = static_cast<float>(row0), Y1 = static_cast<float>(min(v.H, row0 + 4 * kPx) - 1);
+  float X0, X1, Y0, Y1;
+  tile_bounds(tx, ty, v.W, v.H, X0, X1, Y0, Y1);
+  const float S0 = static_cast<float>(row0), S1 = static_cast<float>(min(v.H, row0 + 4 * kPx) - 1);  // the strip's rows
   const uint64_t lt = (1ull << lane) - 1ull;
   float T[kPx], Cr[kPx], Cg[kPx], Cb[kPx], Dz[kPx], V0[kPx], V1[kPx], V2[kPx], Rh[kPx];
   float Aw[kPx];  // sum T alpha, the normalized depth's denominator
@@ -122,7 +131,8 @@ __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const 
         z = geom.depth[g];
         if (geom.feat) fv = reinterpret_cast<const float4*>(geom.feat)[g];
       }
-      keep = !kTest || tile_reachable(m.x, m.y, co.x, co.y, co.z, co.w, X0, X1, Y0, Y1);
+      keep = kCulled || tile_reachable(m.x, m.y, co.x, co.y, co.z, co.w, X0, X1, Y0, Y1);
+      if (kParts > 1) keep = keep && rect_reachable(m.x, m.y, co.x, co.y, co.z, co.w, X0, X1, S0, S1);
       plain = !keep || pair_is_plain(m, co);
     }
     const uint64_t km = __ballot(keep);
@@ -651,9 +661,9 @@ hipError_t launch_render_fwd(const ViewSet& vs, const Geom& geom, const uint32_t
   const bool ch = !vs.table && (vs.one.depth_img || vs.one.vbar_img || vs.one.rho_img);
   auto pick = [&](auto count, auto channels) {
     constexpr bool kCount = decltype(count)::value, kCh = decltype(channels)::value;
-    return parts == 4 ? k_render_fwd<kCount, true, kCh, 1>
-           : parts == 2 ? k_render_fwd<kCount, true, kCh, 2>
-           : culled ? k_render_fwd<kCount, false, kCh, 4> : k_render_fwd<kCount, true, kCh, 4>;
+    return parts == 4   ? (culled ? k_render_fwd<kCount, true, kCh, 1> : k_render_fwd<kCount, false, kCh, 1>)
+           : parts == 2 ? (culled ? k_render_fwd<kCount, true, kCh, 2> : k_render_fwd<kCount, false, kCh, 2>)
+                        : (culled ? k_render_fwd<kCount, true, kCh, 4> : k_render_fwd<kCount, false, kCh, 4>);
   };
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
