@@ -218,13 +218,18 @@ __device__ __forceinline__ float pair_exp2(float qz, float c1, float c0, float d
 }
 
 // A pair whose alpha needs neither the 0.99 clamp nor the test for a positive
-// exponent, for any pixel: o <= 0.99, and a conic far enough from singular
-// that the computed p2 cannot round above 0.  With r = |B| / sqrt(A C),
-// -p2 >= (1 - r) (|q.x| dx^2 + |q.z| dy^2) while the roundings of p2 add at
-// most (2 + 2 r) 2^-24 of the same sum, so r <= 1 - 5e-6 leaves a factor of
-// twenty.  NaNs and infinities fail the test.
+// exponent, for any pixel: |o| <= 0.99, and a conic far enough from singular
+// that the computed p2 cannot round above 0.  With r = |B| / sqrt(A C) and
+// S = |q.x| dx^2 + |q.z| dy^2, -p2 >= (1 - r) S.  Coefficient, products and
+// inner sum round three times in each of the square and the cross term, at
+// most (3 + 3 r) 2^-24 S in all (the outer sum's rounding keeps its sign), so
+// r <= 1 - 4.9e-6 leaves a factor of thirteen.  The walks that take such pairs
+// rely on alpha never being NaN as well: NaNs and infinities fail the test, and
+// so do conics whose terms could overflow to opposite infinities or whose
+// product A C says nothing for having underflowed.
 __device__ __forceinline__ bool pair_is_plain(float2 m, float4 co) {
-  return co.w <= kAlphaMax && co.x > 0.0f && co.z > 0.0f && co.y * co.y <= (co.x * co.z) * 0.99999f &&
+  const float ac = co.x * co.z;
+  return fabsf(co.w) <= kAlphaMax && co.x > 0.0f && ac > 1e-30f && ac < 1e30f && co.y * co.y <= ac * 0.99999f &&
          fabsf(m.x) < 1e9f && fabsf(m.y) < 1e9f;
 }
 
