@@ -169,6 +169,12 @@ __global__ void __launch_bounds__(64) k_feat_fwd(ViewSet vs, Geom geom, const ui
 // position test walk without; two pairs a group here, as four pairs' sums
 // beside the pixels' gradients do not fit the registers.  The order of every
 // sum is that of single pairs.  19 channels, 1M view: 850 -> 770 us.
+// A pair that no pixel of the tile uses has alpha = 0 everywhere, which leaves a
+// pixel's blend unchanged as long as the blended gradient it is scaled with is
+// finite: a vector and upstream gradients of sizes below kTame give one.  In
+// batches that hold more than that (or NaN) the unused pairs' vectors become 0.
+constexpr float kTame = 1e15f;
+
 template <int kNC, bool kCulled>
 __global__ void __launch_bounds__(64) k_feat_bwd(ViewSet vs, Geom geom, Lists lists, const float* __restrict__ feat,
                                                  int64_t ld, int nch, const float* __restrict__ dout, float* rec,
@@ -210,6 +216,7 @@ __global__ void __launch_bounds__(64) k_feat_bwd(ViewSet vs, Geom geom, Lists li
   int last[kPix];
   float thr[kPix];  // alpha a pair needs to be used: 1/255, or infinity outside the image
   int lmax = 0, lmin = INT_MAX;
+  float size = 0.0f;  // of the upstream gradients: the sum of their magnitudes, NaN if one is
 #pragma unroll
   for (int k = 0; k < kPix; ++k) {
     const int py = py0 + 4 * k;
@@ -220,17 +227,21 @@ __global__ void __launch_bounds__(64) k_feat_bwd(ViewSet vs, Geom geom, Lists li
     thr[k] = in ? kAlphaMin : kNever;
     if (in) lmin = min(lmin, last[k]);
 #pragma unroll
-    for (int c = 0; c < kNC; ++c) G[k][c] = (in && c < nch) ? dout[c * HW + o] : 0.0f;
+    for (int c = 0; c < kNC; ++c) {
+      G[k][c] = (in && c < nch) ? dout[c * HW + o] : 0.0f;
+      if (kG == 2) size += fabsf(G[k][c]);
+    }
     rr[k] = 0.0f;  // the blend behind the last contributor: no background for features
     lmax = max(lmax, last[k]);
   }
   lmax = wave_max(lmax);
   lmin = -wave_max(-lmin);
+  const bool tame_tile = __all(size < kTame);
   const uint32_t start = lists.ranges[2 * tile];
   lmax = min(lmax, static_cast<int>(lists.ranges[2 * tile + 1] - start));  // never read past the tile's list
   for (int hi = lmax; hi > 0; hi -= 64) {
     const int lo = max(0, hi - 64);
-    bool keep = false, plain = true;
+    bool keep = false, plain = true, tame = tame_tile;
     uint32_t g = 0;
     float2 m;
     float4 co;
@@ -250,8 +261,13 @@ __global__ void __launch_bounds__(64) k_feat_bwd(ViewSet vs, Geom geom, Lists li
       s_pos[slot] = lo + lane;
       float4 f[kQ];
       load_feature<kNC>(feat, ld, nch, g, f);
+      float size = 0.0f;
 #pragma unroll
-      for (int q = 0; q < kQ; ++q) s_f[slot][q] = f[q];
+      for (int q = 0; q < kQ; ++q) {
+        s_f[slot][q] = f[q];
+        if (kG == 2) size += (fabsf(f[q].x) + fabsf(f[q].y)) + (fabsf(f[q].z) + fabsf(f[q].w));
+      }
+      tame = tame && size < kTame;
     }
     const int cnt = __popcll(km);
     if (lane == cnt && cnt % kG != 0) {  // a padding pair, which no pixel uses
@@ -263,6 +279,24 @@ __global__ void __launch_bounds__(64) k_feat_bwd(ViewSet vs, Geom geom, Lists li
       for (int q = 0; q < kQ; ++q) s_f[lane][q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
     __syncthreads();
+    if (kG == 2 && !__all(tame)) {  // (single pairs skip the unused ones)
+#pragma unroll 1
+      for (int j = 0; j < cnt; ++j) {
+        const float2 gm = s_xy[j];
+        const float4 gq = s_q[j];
+        const float dx = gm.x - fpx;
+        const float c1 = gq.y * dx, c0 = (gq.x * dx) * dx;
+        bool any = false;
+#pragma unroll
+        for (int k = 0; k < kPix; ++k) {
+          const float p2 = pair_exp2(gq.z, c1, c0, gm.y - static_cast<float>(py0 + 4 * k));
+          const float alpha = fminf(kAlphaMax, gq.w * __builtin_amdgcn_exp2f(p2));
+          any = any || (s_pos[j] < last[k] && !(p2 > 0.0f) && !(alpha < kAlphaMin));
+        }
+        if (!__any(any) && lane < kQ) s_f[j][lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      }
+      __syncthreads();
+    }
     uint64_t used = 0;  // pairs of the batch that some pixel uses
     // Pairs j0 + kG - 1 .. j0, as a group of the colour adjoint: kPlain, no pair of
     // the batch needs the clamp or the exponent's sign; kAll, every pixel is
@@ -277,9 +311,9 @@ __global__ void __launch_bounds__(64) k_feat_bwd(ViewSet vs, Geom geom, Lists li
         const float4 gc = s_co[j];
         const float4 gq = s_q[j];
         const int pos = s_pos[j];
-        // alpha of the lane's four pixels as in the colour adjoint; an unused
-        // pair takes alpha = 0, which leaves T (rcp(1) is exact) and the
-        // blend behind it unchanged
+        // alpha of the lane's four pixels as in the colour adjoint; a pixel that
+        // does not use the pair takes alpha = 0, which leaves T (rcp(1) is exact)
+        // and the blend behind it unchanged
         const float dx = gm.x - fpx;
         const float c1 = gq.y * dx, c0 = (gq.x * dx) * dx;
         float au[kPix], gate[kPix];
