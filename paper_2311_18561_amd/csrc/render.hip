@@ -221,35 +221,38 @@ __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const 
         }
         if (!stopped) return;
 #pragma unroll 1
-        for (int j = j0; j < j0 + kGroup; ++j) {
-          const float2 gm = s_xy[j];
-          const float4 gc = s_co[j];
-          const float4 cc = s_rgb[j];
-          const float gz = kCh ? s_z[j] : 0.0f;
-          const float4 gv = kCh ? s_fv[j] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-          const int pos = kTest ? __float_as_int(cc.w) : static_cast<int>(b0 - start) + j + 1;
-          const float dx = gm.x - fpx;
-          const float c1 = gc.y * dx, c0 = (gc.x * dx) * dx;
-          bool on = false;
+        for (int j4 = j0; j4 < j0 + kGroup; j4 += 4) {
+#pragma unroll 1
+          for (int j = j4; j < j4 + 4; ++j) {
+            const float2 gm = s_xy[j];
+            const float4 gc = s_co[j];
+            const float4 cc = s_rgb[j];
+            const float gz = kCh ? s_z[j] : 0.0f;
+            const float4 gv = kCh ? s_fv[j] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            const int pos = kTest ? __float_as_int(cc.w) : static_cast<int>(b0 - start) + j + 1;
+            const float dx = gm.x - fpx;
+            const float c1 = gc.y * dx, c0 = (gc.x * dx) * dx;
+            bool on = false;
 #pragma unroll
-          for (int k = 0; k < kPx; ++k) {
-            if (kCount) evaluated += (thr[k] < 1.0f && j < cnt) ? 1 : 0;
-            const float dy = gm.y - static_cast<float>(py0 + 4 * k);
-            const float p2 = pair_exp2(gc.z, c1, c0, dy);
-            const float raw = gc.w * __builtin_amdgcn_exp2f(p2);
-            const float alpha = kPlain ? raw : fminf(kAlphaMax, raw);
-            const bool pass = !(alpha < thr[k]) && (kPlain || !(p2 > 0.0f));
-            const float Tp = T[k] * (1.0f - alpha);
-            const bool stop = pass && Tp < kTMin, use = pass && !stop;
-            blend(k, cc, gz, gv, use ? alpha * T[k] : 0.0f);
-            T[k] = use ? Tp : T[k];
-            last[k] = use ? pos : last[k];
-            thr[k] = stop ? kNever : thr[k];
-            on = on || thr[k] < 1.0f;
+            for (int k = 0; k < kPx; ++k) {
+              if (kCount) evaluated += (thr[k] < 1.0f && j < cnt) ? 1 : 0;
+              const float dy = gm.y - static_cast<float>(py0 + 4 * k);
+              const float p2 = pair_exp2(gc.z, c1, c0, dy);
+              const float raw = gc.w * __builtin_amdgcn_exp2f(p2);
+              const float alpha = kPlain ? raw : fminf(kAlphaMax, raw);
+              const bool pass = !(alpha < thr[k]) && (kPlain || !(p2 > 0.0f));
+              const float Tp = T[k] * (1.0f - alpha);
+              const bool stop = pass && Tp < kTMin, use = pass && !stop;
+              blend(k, cc, gz, gv, use ? alpha * T[k] : 0.0f);
+              T[k] = use ? Tp : T[k];
+              last[k] = use ? pos : last[k];
+              thr[k] = stop ? kNever : thr[k];
+              on = on || thr[k] < 1.0f;
+            }
+            live = __ballot(on);
           }
-          live = __ballot(on);
+          if (!live) return;  // the next four pairs are not blended: their values may be NaN
         }
-        if (!live) return;
       }
     };
     if (__all(plain)) walk(std::true_type{});
