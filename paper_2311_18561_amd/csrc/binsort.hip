@@ -1594,14 +1594,36 @@ struct RowSort {
   uint32_t *rkeys, *rvals, *skeys, *svals, *hist, *chist, *rowtot, *starts, *chunks, *num_chunks;
 };
 
+// Whether sorting row records beats sorting instances.  It moves every record
+// twice and every instance once; the instance sort moves instances once per 8
+// bits of the tile id and once more, so where rows are short (few columns) or
+// the tile ids take one pass, only launches small enough for the shorter chain
+// of kernels to count gain.  Lists of a driving path of 200k - 500k - 1M - 5M
+// Gaussians, us, by instances against by row records:
+//   16 x 16 tiles (one pass) 136 - 134, 178 - 180, 256 - 266, 1,012 - 1,117
+//   4 x 64 (one pass)        137 - 138, 180 - 194, 266 - 299, 1,086 - 1,326
+//   20 x 15                  158 - 132, 199 - 174, 278 - 268, 1,057 - 1,092
+//   32 x 32                  (300k) 172 - 151, 289 - 276, 1,153 - 1,151
+//   6 x 1,024                164 - 156, 204 - 203, 265 - 289, 997 - 1,047
+//   8 x 512                  162 - 145, 200 - 178, 288 - 261, 1,037 - 978
+//   60 x 40                  (300k) 183 - 158, 330 - 288, 1,358 - 1,195
+// and 1M at 120 x 80 480 - 342, at 128 x 1,024 1,313 - 590.
+static bool rows_pay(const ViewSet& vs) {
+  const int64_t n = vs.total_gauss;
+  if (n <= 1 << 17) return true;
+  if (vs.total_tiles <= 256) return false;
+  if (vs.total_rows > 256 && vs.max_cols < 8) return n <= 1 << 19;
+  return vs.total_tiles > 512 || n <= 3 << 19;
+}
+
 // The tile-row path takes every culled launch whose view widths fit the packed
-// keys, whose tile rows fit one digit (10 bits) and whose tables fit the rows
+// keys, whose tile rows fit one digit (10 bits), whose tables fit the rows
 // scratch, which is sized for the other path (from a capacity of some 100
-// instances a tile row of 120 columns on they do).  It was the faster one at
-// every size measured, from 2,000 Gaussians at 128x96 to 6M.
+// instances a tile row of 120 columns on they do), and which gains by it.
 static bool plan_rows(const ViewSet& vs, const pvg_bins* bins, uint32_t* scratch, RowSort& r) {
   const int64_t cap = bins->capacity;
   if (!bins->tile_cull || vs.total_rows < 1 || vs.total_rows > 1024 || vs.max_cols > kMaxCols) return false;
+  if (!rows_pay(vs)) return false;
   r.nrows = static_cast<int>(vs.total_rows);
   r.ld = vs.max_cols;
   r.cols = cdiv(cap, kRowSort);
