@@ -454,6 +454,11 @@ __global__ void __launch_bounds__(64, 3) k_render_bwd(ViewSet vs, Geom geom, Lis
       float h[kSums][2];  // the pairs' sums folded over the half-waves: pairs 0 | 1 and 2 | 3
 #pragma unroll
       for (int half = 1; half >= 0; --half) {
+        if (!kAll && half == 1 && j0 + 2 >= cnt) {  // both padding, half of the walk where lists are short
+#pragma unroll
+          for (int q = 0; q < kSums; ++q) h[q][1] = 0.0f;
+          continue;
+        }
         float a[2][kSums];
 #pragma unroll
         for (int sub = 1; sub >= 0; --sub) {
