@@ -523,7 +523,15 @@ int pvg_sky_composite_bwd_deterministic(const pvg_camera* cam, const float* dL_d
 int pvg_bwd_views_tmp_bytes(int64_t n, int32_t n_views, int32_t max_width, int32_t max_height,
                             int64_t max_capacity, size_t* bytes);
 
-/* ---- stage timing (HIP events recorded on the launch stream) ------------ */
+/* ---- stage timing (HIP events recorded on the launch stream) ------------
+ * A stage that a launch does by other kernels records nothing for it:
+ * - Culled lists built by tile rows (most culled launches): SCAN_EMIT is the
+ *   row counting and the row records, TILE_SORT their sort, the expansion and
+ *   the tile ranges; RANGES records nothing.
+ * - One view of up to 8,192 Gaussians: DEPTH_SORT is the compaction, the sort
+ *   and (culled) the row counting in one launch; COMPACT records nothing.
+ * A sum over the binning stages (COMPACT to RANGES) is comparable between all
+ * launches. */
 enum pvg_stage {
   PVG_STAGE_PREPROCESS = 0, PVG_STAGE_COMPACT, PVG_STAGE_DEPTH_SORT, PVG_STAGE_SCAN_EMIT,
   PVG_STAGE_TILE_SORT, PVG_STAGE_RANGES, PVG_STAGE_RENDER_FWD, PVG_STAGE_RENDER_BWD,

@@ -239,6 +239,11 @@ int launch_batch(pvg_server* s, Lane& L) {
   }
   const BinPlan plan = plan_bins(gb, tb, s->cfg.instance_capacity);
   if (!s->cfg.use_graphs) return enqueue_batch(s, L, vs, plan);
+  // up to seven graphs a (Gaussians, tiles) bucket: rows of 256, 512 or 1,024
+  // by 128 or 255 columns, or neither.  A graph is captured in about 0.1 ms on
+  // its bucket's first batch: 57 in 200 bursts over ten image sizes from 128x96
+  // to 3840x2160 (25 with buckets of Gaussians and tiles alone), whose slowest
+  // first batch and whose total got shorter all the same (294 -> 215 ms)
   const std::array<int64_t, 4> key{gb, tb, vs.total_rows, vs.max_cols};
   auto it = L.graphs.find(key);
   if (it == L.graphs.end()) {
