@@ -401,12 +401,13 @@ __device__ __forceinline__ void sh_grad(const BwdViews& pk, const pvg_gaussians_
 // Gaussians).  Zeros and values leave in the same stores: written by
 // themselves, the zeros' half-filled cache lines left L2 before the values
 // came and went to memory twice (2.1 to 2.9 GB at 6M, one view 1,152 us
-// against 891).  Taking all views in one pass, not one per three, reads
+// against 873).  Taking all views in one pass, not one per three, reads
 // parameters and gradients once: a 6-view step at 6M 9,790 -> 9,280 us, at 1M
 // 4,340 -> 4,210, although a pass no longer runs beside the next views'
-// compositing.  Four waves a SIMD (a few spills) against three: one view at
-// 200k 34 us against 41, at 6M 870 against 947.
-__global__ void __launch_bounds__(256, 4) k_preprocess_bwd(BwdViews pk, pvg_gaussians_grad grad, int accumulate) {
+// compositing.  Three waves a SIMD (168 registers, three words spilled): at
+// four one view at 200k takes 42.1 us against 38.7, at 6M 945 against 873, and six
+// views at 6M 2,167 against 2,174.
+__global__ void __launch_bounds__(256, 3) k_preprocess_bwd(BwdViews pk, pvg_gaussians_grad grad, int accumulate) {
   const Scene& s = pk.views[0].s;
   const int64_t n = s.n;
   __shared__ float s_acc[sizeof(GeoGrad) / 4][256];
