@@ -301,9 +301,10 @@ __global__ void __launch_bounds__(64) k_render_fwd(ViewSet vs, Geom geom, const 
 // (group_sum_store), which takes a third of the instructions of folding each
 // pair's nine by DPP.  A batch whose pairs cannot clamp (pair_is_plain) walks
 // without the clamp's tests, a group behind every pixel's last contributor
-// without the position's.  Per view, us: 1M 386 -> 310 (channels 491 -> 463),
-// 200k at 960x640 163 -> 136.  Three waves a SIMD (141 registers; channels
-// 168): plain at four 313 and at five, which spills, 333; channels at two 488.
+// without the position's.  Mean per view, us: 1M 382 -> 329 (channels 497 ->
+// 465), 200k at 960x640 164 -> 135.  Three waves a SIMD (141 registers;
+// channels 168, a few words spilled): at four the plain kernel is even at 1M
+// and 4% slower on 1280x720, at five, which spills, 7%; channels at two 5%.
 //
 // The order of every sum is fixed by design, pair by pair and pixel by pixel:
 // near the camera a Gaussian's gradient is the difference of sums many

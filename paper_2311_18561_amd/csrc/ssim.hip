@@ -60,8 +60,8 @@ __device__ __forceinline__ int64_t band_tile(int64_t b, int64_t total) {
 // staged values and 4 rows from 14, in registers, and the row pass's results
 // take the place of the staged maps in LDS, so that six workgroups fit a CU
 // where two did (adjoint: three).  Loads go out together, ahead of the first
-// LDS store.  Per 1920x1280 image of three channels, us: forward 140 -> 58,
-// adjoint 84 -> 58 (their reads and writes alone: 36 and 42).  Tiles of 48
+// LDS store.  Per 1920x1280 image of three channels, us: forward 135 -> 56,
+// adjoint 83 -> 57 (their reads and writes alone: 36 and 42).  Tiles of 48
 // rows 59 and 59, of 24 rows 62 and 60; a branch around each load 72 and 69.
 // Taking (x - y)^2 for x^2 and y^2 lowers the map's error against 64 bits from
 // 6.2e-6 to 4.8e-6 of its norm (640x960, noise 0.1), the gradient's from
